@@ -81,8 +81,10 @@ enum { SPKMC_INIT_RANDOM = 0, SPKMC_INIT_UP = 1, SPKMC_INIT_DOWN = 2 };
 enum { SPKMC_LAYOUT_INT8 = 0, SPKMC_LAYOUT_PACKED = 1 };
 /* Kernel engine.  AUTO picks PERSISTENT when supported (and when the domains
  * fit in one resident launch), else CYCLE.
- * CYCLE: three launches per cycle (bin, select-and-flip, finalize), any layout
- * and size (the only engine for lattices of 2^34 sites or more).
+ * CYCLE: any layout and size (the only engine for lattices of 2^34 sites or
+ * more): three launches per cycle (bin, select-and-flip, finalize), or, where
+ * INT8 lattices and PACKED ones with an octant edge other than 8 and 16 fit in
+ * the chip's LDS (a byte per site), one launch per spkmc_run call.
  * PERSISTENT: one cooperative launch per spkmc_run call with a device-wide R_max
  * exchange every cycle (PACKED layout, h = 8 or 16); every cycle bins the
  * active octant of every domain afresh.  With h = 16 and more lines than one

@@ -3,6 +3,7 @@
 
 #include <string>
 
+#include "resident.hpp"
 #include "spkmc_device.hpp"
 
 namespace spkmc {
@@ -68,6 +69,7 @@ struct spkmc_ctx {
     int primed_grid;
     uint64_t primed_cycle, primed_span;
     int engine;
+    spkmc::ResidentShape res;      // CYCLE engine: the on-chip launch, where the lattice fits
     int grid, block, wg_domains;
     bool failed;
     std::string err;

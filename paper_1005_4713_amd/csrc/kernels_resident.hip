@@ -1,0 +1,677 @@
+// kernels_resident.hip -- the per-cycle engine's lattices that fit on chip: one
+// launch runs many cycles (Sec. 3.1 steps 1-6, Sec. 3.2 steps 4a/4b) with every
+// site's state in LDS, for any octant edge, either spin layout and every variant.
+//
+// What bounds it: a latency chain per cycle (LDS reads, barriers and, with more
+// than one workgroup, the R_max exchange); it reads nothing from memory but
+// other workgroups' words.  Per cycle, records included, against the three
+// launches per cycle it replaces: L = 16, d = 8 (one workgroup) 3.7 us against
+// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 7.2 us against 77, of
+// which binning took 49 (a workgroup per line of 64 sites); L = 72, d = 8, two
+// colours 6.5 us against 58.
+//
+// Layout in LDS, per domain of the workgroup:
+//   * one byte per site, octant-major in canonical order: 8 [up] + (up
+//     neighbours).  A flip then changes its own byte by an exclusive or and each
+//     neighbour's by +-1, whatever the neighbour's spin, so that flips by
+//     different threads commute and every atomic's old value names the class
+//     the site left;
+//   * per octant the sites of each byte value (16-bit halves of 8 words): the
+//     frequency line (step 1) is read from them, nothing is binned.
+// A group of GS lanes owns a frequency line: every lane forms the line's sums,
+// the group counts the selected byte over its octant's words (GS x W words, a
+// contiguous run of W words per lane, W odd so that the lanes fall on different
+// LDS banks) and its lanes then move the six neighbours, the site itself, the
+// spin in memory and the halo copies, one each.
+//
+// Between workgroups: the R_max slots of the persistent kernels (bank n & 1,
+// generation bit 63), and one 64-bit event record per frequency line (cycle in
+// the upper half, bank n & 1).  A workgroup applies the events of the
+// neighbouring domains it does not own to its own sites: before the frequency
+// lines where the colour change makes them matter, else while the other maxima
+// travel.  The records carry their cycle, so no flip has to be waited for.
+#include <string>
+
+#include "persistent_common.hpp"
+#include "resident.hpp"
+
+namespace spkmc {
+
+namespace {
+
+constexpr uint32_t kPadByte = 15;  // bytes past an octant's last site: a value no class has
+
+struct ResidentHead {
+    double r[16];                 // rate of each byte value
+    unsigned long long wmax[16];  // per wavefront: its largest line
+    unsigned long long stat[2];   // this workgroup's counters of cycle n (bank n & 1)
+    double rmax;
+    double lnu;   // -ln u of the next cycle's clock step
+    int colour;   // the next cycle's colour
+    int abort;
+};
+constexpr uint32_t kHeadBytes = 512;
+static_assert(sizeof(ResidentHead) <= kHeadBytes, "head");
+
+// class c (7 [up] + aligned) <-> byte value 8 [up] + up neighbours
+__device__ __forceinline__ int byte_of_class(int c) { return c >= 7 ? c + 1 : 6 - c; }
+
+// Counters of one cycle, packed: fired, of these up spins, sum of aligned counts.
+constexpr unsigned long long kGenBit = 1ull << 63;
+__device__ __forceinline__ unsigned long long stat_of(int cs) {
+    return 1ull | ((unsigned long long)(cs >= 7) << 20) | ((unsigned long long)(cs % 7) << 40);
+}
+
+__device__ __forceinline__ uint32_t match_bits(uint32_t w, uint32_t pat) {  // bit 4 of every byte equal to the pattern's
+    return (0x10101010u - (w ^ pat)) & 0x10101010u;
+}
+
+struct Site {
+    int c[3];
+};
+__device__ __forceinline__ Site site_of(uint32_t q, const ResidentArgs &A) {
+    const uint32_t yz = (uint32_t)(((uint64_t)q * A.hinv) >> 32);  // q / h, exact for q < 2^16
+    const uint32_t z = (uint32_t)(((uint64_t)yz * A.hinv) >> 32);
+    return Site{{(int)(q - yz * (uint32_t)A.g.h), (int)(yz - z * (uint32_t)A.g.h), (int)z}};
+}
+__device__ __forceinline__ uint32_t index_of(const Site &s, int h) {
+    return (uint32_t)(s.c[0] + h * (s.c[1] + h * s.c[2]));
+}
+
+// Inclusive prefix sum over the GS lanes of a group.
+template <int GS>
+__device__ __forceinline__ uint32_t group_scan(uint32_t v) {
+    v = row_scan(v);
+    if constexpr (GS == 64) {
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast15, 0xA, 0xF, true);
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kRowBcast31, 0xC, 0xF, true);
+    }
+    return v;
+}
+
+// The spin (1 = up) of site (k, o, s) with s possibly one step outside octant o
+// along axis `ax`, from the lattice in memory.
+__device__ __forceinline__ uint32_t spin_near(const Geom &g, uint32_t k, const int (&kc)[3], int o, Site s, int ax) {
+    if (g.layout == SPKMC_LAYOUT_INT8) {
+        int X[3];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            X[a] = kc[a] * g.d + ((o >> a) & 1) * g.h + s.c[a];
+            X[a] = X[a] < 0 ? g.L - 1 : X[a] == g.L ? 0 : X[a];
+        }
+        return g.spin8[(uint32_t)X[0] + (uint32_t)g.L * ((uint32_t)X[1] + (uint32_t)g.L * (uint32_t)X[2])] > 0;
+    }
+    const int v = ax < 0 ? 0 : s.c[ax];
+    if (ax >= 0 && (v < 0 || v == g.h)) {  // the octant's own halo copy
+        const int u0 = ax == 0 ? s.c[1] : s.c[0], u1 = ax == 2 ? s.c[1] : s.c[2];
+        const uint32_t b = (uint32_t)(2 * ax + (v < 0 ? 0 : 1)) * g.h2 + (uint32_t)(u0 + g.h * u1);
+        return (g.F[((uint64_t)k * 8 + (uint64_t)o) * g.fwpo + (b >> 5)] >> (b & 31)) & 1u;
+    }
+    const uint32_t q = index_of(s, g.h);
+    return (g.A[((uint64_t)k * 8 + (uint64_t)o) * g.wpo + (q >> 5)] >> (q & 31)) & 1u;
+}
+
+}  // namespace
+
+// GS: lanes per frequency line.
+template <int GS>
+__global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
+    extern __shared__ uint4 lds_raw[];
+    const Geom &g = A.g;
+    const uint32_t gid = blockIdx.x, G = A.G;
+    const uint32_t kbase = gid * A.D;
+    const uint32_t nown = kbase >= g.K ? 0u : (g.K - kbase < A.D ? g.K - kbase : A.D);
+    const uint32_t lpd = g.lpd, NL = g.K * lpd, lbase = kbase * lpd, nl = nown * lpd;
+    const int h = g.h;
+    const uint32_t ow = A.ow;
+    ResidentHead &sh = *reinterpret_cast<ResidentHead *>(lds_raw);
+    uint32_t *const cnt = reinterpret_cast<uint32_t *>(lds_raw) + kHeadBytes / 4;  // [domain][octant][8]
+    uint32_t *const nbr = cnt + A.D * 64;                                          // [domain][6]
+    uint32_t *const cls = nbr + A.D * 6;                                           // [domain][octant][ow]
+    const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6, nwaves = nthr >> 6;
+    const int l = tid & (GS - 1);
+    const uint32_t group = (uint32_t)tid / GS, groups = (uint32_t)nthr / GS;
+    const bool svc = wave == nwaves - 1;  // records, the clock and the next cycle's draw
+    DevState *const st = g.st;
+    const uint64_t n0 = A.n0, n_end = A.n0 + A.ncycles;
+    const bool rmax_all = (g.variant & SPKMC_VARIANT_RMAX_ALL) != 0;
+    const bool bound = (g.variant & SPKMC_VARIANT_RMAX_BOUND) != 0;
+    const double clock_s = lpd == 4 ? 2.0 : 8.0;
+
+    // --- set-up: tables, then every own site's byte from the spins and halos
+    if (tid < 16) sh.r[tid] = tid < 7 ? g.r[6 - tid] : tid >= 8 && tid < 15 ? g.r[tid - 1] : 0.0;
+    if (tid == 0) {
+        sh.abort = 0;
+        sh.stat[0] = sh.stat[1] = 0;
+    }
+    for (uint32_t i = (uint32_t)tid; i < nown * 6; i += nthr) {
+        const int dir = (int)(i % 6), a = dir >> 1;
+        const DomainCoord c = dcoord(kbase + i / 6, g.nd);
+        int kc[3] = {c.kx, c.ky, c.kz};
+        kc[a] = (dir & 1) ? wrapp(kc[a], g.nd) : wrapm(kc[a], g.nd);
+        nbr[i] = dindex(kc[0], kc[1], kc[2], g.nd);
+    }
+    for (uint32_t i = (uint32_t)tid; i < nown * 8 * ow; i += nthr) {
+        const uint32_t oct = i / ow, k = kbase + (oct >> 3);
+        const int o = (int)(oct & 7u);
+        const DomainCoord dc = dcoord(k, g.nd);
+        const int kc[3] = {dc.kx, dc.ky, dc.kz};
+        uint32_t word = 0;
+#pragma unroll 1
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t q = (i - oct * ow) * 4 + (uint32_t)b;
+            uint32_t v = kPadByte;
+            if (q < g.h3) {
+                const Site s = site_of(q, A);
+                v = 8u * spin_near(g, k, kc, o, s, -1);
+#pragma unroll
+                for (int dir = 0; dir < 6; ++dir) {
+                    Site t = s;
+                    t.c[dir >> 1] += (dir & 1) ? 1 : -1;
+                    v += spin_near(g, k, kc, o, t, dir >> 1);
+                }
+            }
+            word |= v << (8 * b);
+        }
+        cls[i] = word;
+    }
+    __syncthreads();
+    for (uint32_t ob = 0; ob < nown * 8; ob += groups) {  // every octant's counts, a group each
+        const uint32_t oct = ob + group;
+        for (int vw = 0; vw < 8; ++vw) {
+            uint32_t c0 = 0, c1 = 0;
+            if (oct < nown * 8)
+                for (uint32_t p = (uint32_t)l; p < ow; p += GS) {
+                    const uint32_t w = cls[oct * ow + p];
+                    c0 += __builtin_popcount(match_bits(w, 0x02020202u * (uint32_t)vw));
+                    if (vw < 7) c1 += __builtin_popcount(match_bits(w, 0x02020202u * (uint32_t)vw + 0x01010101u));
+                }
+            const uint32_t both = group_scan<GS>(c0 | (c1 << 16));  // a count stays below 2^16
+            if (l == GS - 1 && oct < nown * 8) cnt[oct * 8 + vw] = both;
+        }
+    }
+
+    // a site's byte moves by dn (its neighbour flipped)
+    auto bump = [&](uint32_t oct, uint32_t q, int dn) {
+        const uint32_t shift = 8 * (q & 3);
+        const uint32_t old = (atomicAdd(&cls[oct * ow + (q >> 2)], (uint32_t)dn << shift) >> shift) & 0xFFu;
+        const uint32_t now = old + (uint32_t)dn;
+        atomicAdd(&cnt[oct * 8 + (old >> 1)], 0u - (1u << (16 * (old & 1))));
+        atomicAdd(&cnt[oct * 8 + (now >> 1)], 1u << (16 * (now & 1)));
+    };
+    // The events of cycle m (colour sp) in neighbouring domains of other workgroups,
+    // by threads first, first + step, ...
+    auto apply_events = [&](uint64_t m, int sp, uint32_t first, uint32_t step) {
+        const uint32_t per = lpd == 1 ? 3u : 12u;
+        const uint64_t *bank = A.rec + (m & 1) * (uint64_t)NL;
+        for (uint32_t i = first; i < nown * per; i += step) {
+            const uint32_t ld = i / per, e = i - ld * per;
+            int dir, o;  // the neighbour's direction, and its octant that touches this domain
+            if (lpd == 1) {
+                dir = 2 * (int)e + (((sp >> e) & 1) ? 0 : 1);
+                o = sp;
+            } else {
+                dir = (int)(e >> 1);
+                const int a = dir >> 1, ba = (dir & 1) ? 0 : 1, b1 = (int)(e & 1), b2 = sp ^ ba ^ b1;
+                const int x1 = a == 0 ? 1 : 0, x2 = a == 2 ? 1 : 2;
+                o = (ba << a) | (b1 << x1) | (b2 << x2);
+            }
+            const int a = dir >> 1, below = (dir & 1) ? 0 : 1;  // below: the neighbour's upper layer touches
+            const uint32_t pk = nbr[ld * 6 + dir];
+            if (pk - kbase < nown) continue;
+            const uint64_t *p = bank + (lpd == 1 ? pk : 4 * pk + (uint32_t)(o >> 1));
+            uint64_t v = ld64(p);
+            if ((uint32_t)(v >> 32) != (uint32_t)(m + 1)) {
+                const uint64_t start = now_ticks();
+                while ((uint32_t)((v = ld64(p)) >> 32) != (uint32_t)(m + 1)) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
+                        atomicOr(&st->error, kErrFlagTimeout);
+                        sh.abort = 1;
+                        break;
+                    }
+                }
+                if ((uint32_t)(v >> 32) != (uint32_t)(m + 1)) break;
+            }
+            const uint32_t ev = (uint32_t)v;
+            if (!(ev >> 31)) continue;
+            Site s = site_of(ev & 0xFFFFu, A);
+            if (s.c[a] != (below ? h - 1 : 0)) continue;
+            s.c[a] = below ? 0 : h - 1;
+            bump(ld * 8 + (uint32_t)(o ^ (1 << a)), index_of(s, h), (ev >> 30) & 1u ? -1 : 1);
+        }
+    };
+    // running sums of line f's frequency line (classes in order; with the all-octant
+    // maximum the value returned is the largest line among the octants it stands for)
+    auto line_oct = [&](uint32_t f, int s) { return lpd == 1 ? s : two_colour_octant(s, f & 3u); };
+    auto sums = [&](uint32_t oct, double (&acc)[14]) {
+        uint32_t w[8];
+        const uint4 *c4 = reinterpret_cast<const uint4 *>(&cnt[oct * 8]);
+        const uint4 x = c4[0], y = c4[1];
+        w[0] = x.x, w[1] = x.y, w[2] = x.z, w[3] = x.w, w[4] = y.x, w[5] = y.y, w[6] = y.z, w[7] = y.w;
+        double a = 0.0;
+#pragma unroll
+        for (int c = 0; c < 14; ++c) {
+            const int v = c >= 7 ? c + 1 : 6 - c;
+            const uint32_t cc = (v & 1) ? w[v >> 1] >> 16 : w[v >> 1] & 0xFFFFu;
+            const double term = (double)cc * sh.r[v];
+            a = a + term;
+            acc[c] = a;
+        }
+        return a;
+    };
+
+    // the record keeper's totals since launch start (workgroup 0, service wavefront:
+    // each lane sums the workgroups it reads)
+    long long totF = 0, totU = 0, totA = 0;
+    const bool keeper = gid == 0 && svc;
+    double t = 0.0;
+    uint64_t fired0 = 0, nulls0 = 0, recs = 0, next_rec = ~0ull;
+    int64_t M0 = 0, B0 = 0;
+    if (keeper) {
+        fired0 = st->fired;
+        nulls0 = st->nulls;
+        M0 = st->M;
+        B0 = st->B;
+        t = st->t;
+        recs = st->rec_count;
+        if (A.obs_every) next_rec = (n0 / A.obs_every + 1) * A.obs_every;
+    }
+    auto add_stat = [&](unsigned long long v) {
+        totF += (long long)(v & 0xFFFFFu);
+        totU += (long long)((v >> 20) & 0xFFFFFu);
+        totA += (long long)((v >> 40) & 0x7FFFFFu);
+    };
+    // counters of cycle m into the totals (every workgroup has finished it, or is about to)
+    auto gather = [&](uint64_t m) {
+        if (G == 1) {
+            if (lane == 0) add_stat(sh.stat[m & 1]);
+            return;
+        }
+        const unsigned long long gen = ((m >> 1) & 1) << 63;
+        for (uint32_t w = (uint32_t)lane; w < G; w += 64) {
+            const uint64_t *p = A.part + (m & 1) * (uint64_t)G + w;
+            unsigned long long v = ld64(p);
+            if ((v & kGenBit) != gen) {
+                const uint64_t start = now_ticks();
+                while (((v = ld64(p)) & kGenBit) != gen) {
+                    __builtin_amdgcn_s_sleep(1);
+                    if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
+                        atomicOr(&st->error, kErrFlagTimeout);
+                        sh.abort = 1;
+                        return;
+                    }
+                }
+            }
+            add_stat(v);
+        }
+    };
+    // the state after `cyc` cycles: the ring record, or at the end the counters
+    auto keep = [&](uint64_t cyc, bool record, bool final) {
+        long long F = totF, U = totU, Al = totA;
+        for (int o = 32; o > 0; o >>= 1) {
+            F += __shfl_xor(F, o);
+            U += __shfl_xor(U, o);
+            Al += __shfl_xor(Al, o);
+        }
+        if (lane != 0) return;
+        spkmc_record r;
+        r.cycle = cyc;
+        r.fired = fired0 + (uint64_t)F;
+        r.nulls = nulls0 + (uint64_t)NL * (cyc - n0) - (uint64_t)F;
+        r.t = t;
+        r.M = M0 + 2 * F - 4 * U;   // an up spin takes 2 from M, a down spin adds 2
+        r.B = B0 + 12 * F - 4 * Al;  // six bonds, `aligned` of them with the old spin
+        if (record) {
+            g.rec[recs % g.rec_cap] = r;
+            recs += 1;
+        }
+        if (final) {
+            st->cycle = cyc;
+            st->fired = r.fired;
+            st->nulls = r.nulls;
+            st->t = t;
+            st->M = r.M;
+            st->B = r.B;
+            st->rec_count = recs;
+        }
+    };
+
+    const CycleDraw cd0 = cycle_draw(g.seed, n0, lpd == 4);
+    int s = cd0.colour, prev = -1;
+    double lnu = svc ? -log(cd0.ut) : 0.0;
+    const bool one = nl <= groups;  // a single round of lines: sums and draws stay in registers
+    __syncthreads();
+
+    for (uint64_t n = n0; n < n_end; ++n) {
+        // --- step 6: events of the previous cycle in other workgroups' domains, now where
+        // the frequency lines of this cycle can see them
+        bool pending = G > 1 && n > n0;
+        if (pending) {
+            const int diff = s ^ prev;
+            if (rmax_all || (lpd == 4 ? diff != 0 : diff && !(diff & (diff - 1)))) {
+                apply_events(n - 1, prev, (uint32_t)tid, (uint32_t)nthr);
+                pending = false;
+                __syncthreads();
+                if (sh.abort) break;
+            }
+        }
+        // --- steps 1 and 2: the frequency lines and the workgroup's largest
+        double acc[14], m = 0.0;
+        for (uint32_t f = group; f < nl; f += groups) {
+            const uint32_t dom8 = (lpd == 1 ? f : f >> 2) * 8;
+            const int o = line_oct(f, s);
+            if (rmax_all)
+                for (int oo = 0; oo < 8; ++oo)
+                    if (lpd == 1 || oo == (o ^ 1)) m = fmax(m, sums(dom8 + (uint32_t)oo, acc));
+            m = fmax(m, sums(dom8 + (uint32_t)o, acc));
+        }
+        if (!bound) {
+            double v = m;
+            if constexpr (GS == 16) {  // one value per row
+                v = fmax(v, dpp_f64<kRowBcast15, 0xA>(v));
+                v = fmax(v, dpp_f64<kRowBcast31, 0xC>(v));
+            }
+            if (lane == 63) sh.wmax[wave] = double_to_bits(v);
+        }
+        __syncthreads();
+        const uint64_t gen = ((n >> 1) & 1) << 63;
+        U4 dw{};
+        auto draw = [&](uint32_t f) {
+            const uint32_t line = lbase + f;
+            return philox10((uint32_t)n, (uint32_t)(n >> 32), lpd == 1 ? line : line >> 2, (uint32_t)line_oct(f, s), g.seed);
+        };
+        if (G > 1 && wave == 0) {
+            // publish, then poll every workgroup's slot (the fixed bound exchanges zeros:
+            // the exchange also keeps the workgroups within a cycle of one another)
+            double v = !bound && lane < nwaves ? bits_to_double(sh.wmax[lane < 16 ? lane : 15]) : 0.0;
+            v = wave_max_nonneg(v);
+            uint64_t *bank = A.slot + (n & 1) * (uint64_t)G;
+            if (lane == 63) st64(&bank[gid], double_to_bits(v) | gen);
+            double best = 0.0;
+            const uint64_t start = now_ticks();
+            for (uint32_t base = 0; base < G; base += 256) {
+                uint64_t sv[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = base + (uint32_t)(i * 64 + lane);
+                    sv[i] = w < G ? ld64(&bank[w]) : gen;
+                }
+                for (;;) {
+                    bool all = true;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t w = base + (uint32_t)(i * 64 + lane);
+                        if ((sv[i] & kGenBit) != gen) {
+                            all = false;
+                            sv[i] = ld64(&bank[w]);
+                        }
+                    }
+                    if (__all(all)) break;
+                    if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
+                        atomicOr(&st->error, kErrBarrierTimeout);
+                        sh.abort = 1;
+                        break;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) best = fmax(best, bits_to_double(sv[i] & ~kGenBit));
+            }
+            best = wave_max_nonneg(best);
+            if (lane == 63) sh.rmax = best;
+        }
+        if (svc) {
+            if (lane == 0) {
+                const CycleDraw nd = cycle_draw(g.seed, n + 1, lpd == 4);
+                sh.colour = nd.colour;
+                sh.lnu = -log(nd.ut);
+            }
+            if (gid == 0 && n > n0) {
+                gather(n - 1);
+                if (n == next_rec) {
+                    if (g.rec_cap) keep(n, true, false);
+                    next_rec += A.obs_every;
+                }
+                if (G == 1 && lane == 0) sh.stat[(n - 1) & 1] = 0;
+            }
+        } else if (wave != 0) {
+            if (pending) apply_events(n - 1, prev, (uint32_t)tid - 64, (uint32_t)nthr - 128);
+        }
+        if (one) dw = draw(group < nl ? group : 0);
+        if (G > 1) {
+            __syncthreads();
+            if (sh.abort) break;
+        }
+        double Rmax;
+        if (bound) {
+            Rmax = g.rbound;
+        } else if (G > 1) {
+            Rmax = sh.rmax;
+        } else {
+            uint64_t b = 0;
+            for (int w = 0; w < nwaves; ++w) b = sh.wmax[w] > b ? sh.wmax[w] : b;
+            Rmax = bits_to_double(b);
+        }
+
+        // --- steps 3, 4 and 4b, and the flips
+        for (uint32_t fb = 0; fb < nl; fb += groups) {
+            const uint32_t f = fb + group;
+            const bool valid = f < nl;
+            const uint32_t fc = valid ? f : 0;
+            const uint32_t ld = lpd == 1 ? fc : fc >> 2;
+            const int o = line_oct(fc, s);
+            const uint32_t oct = ld * 8 + (uint32_t)o;
+            if (!one) {
+                dw = draw(fc);
+                (void)sums(oct, acc);
+            }
+            const double target = unit53(dw.x, dw.y) * Rmax;
+            int cs = -1;
+#pragma unroll
+            for (int c = 13; c >= 0; --c) cs = target < acc[c] ? c : cs;
+            if (!valid) cs = -1;
+            // the j-th site of the class in canonical order
+            const uint32_t v = (uint32_t)byte_of_class(cs < 0 ? 0 : cs), pat = v * 0x01010101u;
+            const uint32_t cw = cnt[oct * 8 + (v >> 1)];
+            const uint32_t j = mul_index(dw.z, (v & 1) ? cw >> 16 : cw & 0xFFFFu);
+            const uint32_t *const ocls = cls + oct * ow;
+            const uint32_t p0 = (uint32_t)l * A.W, p1 = p0 + A.W < ow ? p0 + A.W : ow;
+            uint32_t mine = 0;
+            for (uint32_t p = p0; p < p1; ++p) mine += __builtin_popcount(match_bits(ocls[p], pat));
+            const uint32_t incl = group_scan<GS>(mine), excl = incl - mine;
+            const bool here = cs >= 0 && j >= excl && j < incl;
+            uint32_t q = 0;
+            if (here) {
+                uint32_t rank = j - excl;
+                uint32_t p = p0, mb = match_bits(ocls[p], pat);
+                for (;;) {
+                    const uint32_t c = __builtin_popcount(mb);
+                    if (rank < c || p + 1 >= p1) break;
+                    rank -= c;
+                    mb = match_bits(ocls[++p], pat);
+                }
+                for (; rank; --rank) mb &= mb - 1;
+                q = 4 * p + ((uint32_t)__builtin_ctz(mb | 0x80000000u) >> 3);
+            }
+            uint64_t bal = __ballot(here);
+            if constexpr (GS == 16) bal = (bal >> (lane & 48)) & 0xFFFFu;
+            const int src = bal ? __builtin_ctzll(bal) : 0;
+            q = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((GS == 16 ? (lane & 48) : 0) + src) << 2), (int)q);
+            const bool event = bal != 0;
+            if (cs >= 0 && !event && l == 0) atomicOr(&st->error, kErrSelect);  // counts disagree with the bytes
+            if (G > 1 && valid && l == 7)
+                st64(A.rec + (n & 1) * (uint64_t)NL + lbase + f,
+                     ((uint64_t)(uint32_t)(n + 1) << 32) |
+                         (event ? 0x80000000u | ((uint32_t)(cs >= 7) << 30) | q : 0u));
+            if (!event) continue;
+            const int up = cs >= 7, dn = up ? -1 : 1;
+            const Site sc = site_of(q, A);
+            if (l < 6) {
+                // the neighbour in direction l, where this workgroup owns it
+                const int a = l >> 1, side = l & 1;
+                Site t = sc;
+                uint32_t toct = oct;
+                const int x = (a == 0 ? sc.c[0] : a == 1 ? sc.c[1] : sc.c[2]) + (side ? 1 : -1);
+                int to = x;
+                if (x < 0 || x == h) {
+                    to = side ? 0 : h - 1;
+                    uint32_t tl = ld;
+                    if (((o >> a) & 1) == side) tl = nbr[ld * 6 + l] - kbase;
+                    toct = tl < nown ? tl * 8 + (uint32_t)(o ^ (1 << a)) : ~0u;
+                }
+                if (a == 0) t.c[0] = to;
+                else if (a == 1) t.c[1] = to;
+                else t.c[2] = to;
+                if (toct != ~0u) bump(toct, index_of(t, h), dn);
+            } else if (l == 6) {
+                atomicXor(&cls[oct * ow + (q >> 2)], 8u << (8 * (q & 3)));
+                const uint32_t now = v ^ 8u;
+                atomicAdd(&cnt[oct * 8 + (v >> 1)], 0u - (1u << (16 * (v & 1))));
+                atomicAdd(&cnt[oct * 8 + (now >> 1)], 1u << (16 * (now & 1)));
+            } else if (l == 8) {
+                atomicAdd(&sh.stat[n & 1], stat_of(cs));
+                if (g.layout == SPKMC_LAYOUT_INT8) {
+                    const DomainCoord dc = dcoord(kbase + ld, g.nd);
+                    const uint32_t X = (uint32_t)(dc.kx * g.d + (o & 1) * h + sc.c[0]);
+                    const uint32_t Y = (uint32_t)(dc.ky * g.d + ((o >> 1) & 1) * h + sc.c[1]);
+                    const uint32_t Z = (uint32_t)(dc.kz * g.d + ((o >> 2) & 1) * h + sc.c[2]);
+                    g.spin8[X + (uint32_t)g.L * (Y + (uint32_t)g.L * Z)] = (int8_t)(up ? -1 : 1);
+                } else {
+                    flip_word(g.A + ((uint64_t)(kbase + ld) * 8 + (uint64_t)o) * g.wpo + (q >> 5), 1u << (q & 31));
+                }
+            } else if (l >= 9 && l < 12 && g.layout == SPKMC_LAYOUT_PACKED) {
+                // the halo copy of the octant across a boundary layer the site lies on
+                const int a = l - 9, x = a == 0 ? sc.c[0] : a == 1 ? sc.c[1] : sc.c[2];
+                if (x == 0 || x == h - 1) {
+                    const int side = x == 0 ? 0 : 1;  // packed octants have h >= 4
+                    const uint32_t kt = ((o >> a) & 1) == side ? nbr[ld * 6 + 2 * a + side] : kbase + ld;
+                    const int u0 = a == 0 ? sc.c[1] : sc.c[0], u1 = a == 2 ? sc.c[1] : sc.c[2];
+                    const uint32_t b = (uint32_t)(2 * a + (side ? 0 : 1)) * g.h2 + (uint32_t)(u0 + h * u1);
+                    flip_word(g.F + ((uint64_t)kt * 8 + (uint64_t)(o ^ (1 << a))) * g.fwpo + (b >> 5), 1u << (b & 31));
+                }
+            }
+        }
+        // --- step 5, in the record keeper's wavefront (the others need no clock)
+        if (svc) {
+            t = t + lnu / (clock_s * Rmax);
+            lnu = sh.lnu;
+        }
+        prev = s;
+        __syncthreads();
+        s = sh.colour;  // next written after the coming barrier
+        if (G > 1 && tid == 0) {
+            st64(A.part + (n & 1) * (uint64_t)G + gid, sh.stat[n & 1] | gen);
+            sh.stat[n & 1] = 0;
+        }
+    }
+    __syncthreads();
+    if (keeper && !sh.abort) {
+        gather(n_end - 1);
+        if (!sh.abort) keep(n_end, n_end == next_rec && g.rec_cap, true);
+    }
+}
+
+// Slots and counters marked with a generation no cycle of the launch expects first,
+// records with a cycle none expects.
+__global__ void k_resident_prep(ResidentArgs A) {
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t NL = (uint64_t)A.g.K * A.g.lpd;
+    if (i < 2 * NL) A.rec[i] = A.n0 << 32;
+    if (i < A.G)
+        for (uint64_t nb = A.n0; nb < A.n0 + 2; ++nb) {
+            const uint64_t v = (((nb >> 1) + 1) & 1) << 63;
+            A.slot[(nb & 1) * A.G + i] = v;
+            A.part[(nb & 1) * A.G + i] = v;
+        }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+static void *resident_kernel(int gs) {
+    return gs == 16 ? reinterpret_cast<void *>(&k_resident<16>) : reinterpret_cast<void *>(&k_resident<64>);
+}
+
+bool resident_configure(const Geom &g, ResidentShape &out) {
+    out = ResidentShape{};
+    // octants of 8 and 16 in packed form have the row and slab kernels; counts are 16-bit
+    if (g.layout == SPKMC_LAYOUT_PACKED && (g.h == 8 || g.h == 16)) return false;
+    if (g.h3 >= (1u << 16)) return false;
+    int dev = 0, cus = 0, lds = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return false;
+    const uint32_t ow = (g.h3 + 3) / 4;
+    const uint64_t per_domain = 64 * 4 + 6 * 4 + 8ull * ow * 4;
+    const uint64_t room = ((uint64_t)lds - kHeadBytes) / per_domain;  // domains one workgroup holds
+    if (room == 0) return false;
+    const int gs = ow <= 128 ? 16 : 64;
+    const uint64_t lines = (uint64_t)g.K * g.lpd;
+    // one workgroup while its wavefronts take the lines in a few rounds (no exchange);
+    // else as many as give each a round of kLinesPerWg lines, up to one per CU
+    uint64_t G = 1;
+    if (g.K > room || lines * gs > 4096) {
+        const uint64_t per_wg = gs == 16 ? kResidentLines : 15;  // 15 groups of 64 lanes and the service wavefront
+        G = (lines + per_wg - 1) / per_wg;
+        const uint64_t need = (g.K + room - 1) / room;
+        G = G < need ? need : G;
+        G = G < 2 ? 2 : G;
+        G = G > (uint64_t)cus ? (uint64_t)cus : G;
+        G = G > g.K ? g.K : G;
+    }
+    const uint64_t D = (g.K + G - 1) / G;
+    if (D > room) return false;
+    G = (g.K + D - 1) / D;
+    uint64_t thr = D * g.lpd * gs;
+    thr = (thr + 63) / 64 * 64 + 64;  // a service wavefront beside the lines'
+    thr = thr < 192 ? 192 : thr > 1024 ? 1024 : thr;
+    out.G = (int)G;
+    out.D = (int)D;
+    out.gs = gs;
+    out.block = (int)thr;
+    out.lds = (size_t)(kHeadBytes + D * per_domain);
+    void *kern = resident_kernel(gs);
+    (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out.lds);
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, out.block, out.lds) != hipSuccess || occ < 1) {
+        (void)hipGetLastError();
+        return false;
+    }
+    (void)hipGetLastError();
+    out.ok = true;
+    return true;
+}
+
+hipError_t launch_resident(const Geom &g, const ResidentShape &shape, uint64_t n0, uint64_t ncycles,
+                           uint32_t obs_every, bool prep, hipStream_t stream) {
+    ResidentArgs A;
+    A.g = g;
+    const uint64_t lines = (uint64_t)g.K * g.lpd;
+    // the per-cycle engine's histograms (8 words per line), unused here: two banks of
+    // records, then the slots and the counters (4 words per workgroup, G <= lines)
+    A.rec = reinterpret_cast<uint64_t *>(g.hist);
+    A.slot = A.rec + 2 * lines;
+    A.part = A.slot + 2 * (uint64_t)shape.G;
+    A.n0 = n0;
+    A.ncycles = ncycles;
+    A.obs_every = obs_every;
+    A.G = (uint32_t)shape.G;
+    A.D = (uint32_t)shape.D;
+    A.ow = (g.h3 + 3) / 4;
+    A.W = ((A.ow + (uint32_t)shape.gs - 1) / (uint32_t)shape.gs) | 1u;
+    A.hinv = g.h == 1 ? 0u : (uint32_t)(((1ull << 32) + (uint64_t)g.h - 1) / (uint64_t)g.h);
+    void *kern = resident_kernel(shape.gs);
+    void *args[] = {&A};
+    if (shape.G == 1)
+        return hipLaunchKernel(kern, dim3(1), dim3(shape.block), args, shape.lds, stream);
+    if (prep) {
+        const uint64_t blocks = (2 * lines + 255) / 256;
+        hipLaunchKernelGGL(k_resident_prep, dim3((uint32_t)blocks), dim3(256), 0, stream, A);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipLaunchCooperativeKernel(kern, dim3(shape.G), dim3(shape.block), args, (uint32_t)shape.lds, stream);
+}
+
+}  // namespace spkmc

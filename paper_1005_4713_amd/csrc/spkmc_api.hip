@@ -271,6 +271,8 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     }
     }
 
+    if (c->engine == SPKMC_ENGINE_CYCLE) (void)resident_configure(g, c->res);
+
     hipError_t e;
     if ((e = hipMemsetAsync(c->dev, 0, lp.off_spin, c->stream)) != hipSuccess) return hip_fail(c, e, "hipMemsetAsync");
     if ((e = hipMemcpyAsync(c->dev + lp.off_rates, g.r, sizeof g.r, hipMemcpyHostToDevice, c->stream)) != hipSuccess)
@@ -279,6 +281,15 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     if ((e = launch_faces(g, c->stream)) != hipSuccess) return hip_fail(c, e, "face kernel");
     if ((e = launch_observables(g, c->stream)) != hipSuccess) return hip_fail(c, e, "observables kernel");
     return SPKMC_OK;
+}
+
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
 }
 
 spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
@@ -303,7 +314,21 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
         c->primed_grid = c->grid;
         c->cycle += ncycles;
         c->primed_cycle = c->cycle;
+    } else if (c->res.ok && !capturing(c->stream)) {
+        // the lattice fits on chip: the cycles in one launch (a stream capture takes no
+        // cooperative launch and gets the per-cycle kernels below)
+        const bool primed = c->primed_grid == c->res.G && c->primed_cycle == c->cycle && c->primed_span >= 2;
+        e = launch_resident(c->g, c->res, c->cycle, ncycles, obs_every, !primed, c->stream);
+        if (e != hipSuccess) {
+            c->primed_grid = 0;
+            return hip_fail(c, e, "on-chip kernel launch");
+        }
+        c->primed_span = (primed ? c->primed_span : 0) + ncycles;
+        c->primed_grid = c->res.G;
+        c->cycle += ncycles;
+        c->primed_cycle = c->cycle;
     } else {
+        c->primed_grid = 0;
         // PACKED lattices with octant edge 16 run the slab kernels, whose counts
         // are binned afresh at the start of every run
         const bool slab = slab_rows_supported(c->g);

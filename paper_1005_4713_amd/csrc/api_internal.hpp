@@ -7,6 +7,8 @@
 #include "spkmc_device.hpp"
 
 namespace spkmc {
+// Set-up: the buffer's first `bytes` (state header to scratch) cleared and the rates written.
+hipError_t launch_clear(const Geom &g, size_t bytes, hipStream_t stream);
 hipError_t launch_init(const Geom &g, int init, hipStream_t stream);
 hipError_t launch_faces(const Geom &g, hipStream_t stream);
 hipError_t launch_observables(const Geom &g, hipStream_t stream);

@@ -12,6 +12,8 @@
 //   k_finalize one thread: clock (step 5), counters, observation record.
 // These kernels are generic over the spin layout and serve as the reference
 // launch shape for the persistent engine.
+#include <type_traits>
+
 #include "api_internal.hpp"
 #include "spkmc_device.hpp"
 
@@ -27,6 +29,38 @@ __global__ void k_init_int8(Geom g, int init) {
     for (int i = 0; i < 128 && first + i < g.N; ++i) {
         int v = init == SPKMC_INIT_UP ? 1 : init == SPKMC_INIT_DOWN ? -1 : ((words[i >> 5] >> (i & 31)) & 1u) ? 1 : -1;
         g.spin8[first + i] = (int8_t)v;
+    }
+}
+
+// The random start of a packed lattice of octant edge H (8 or 16): one thread per
+// 128-site block of the linear order, whose Philox words are 128 / H whole octant
+// rows, each stored as one H-bit piece (a row starts at a multiple of H, so no
+// piece straddles a block).  A thread per packed word instead draws the block of
+// each of its rows, every block 128 / H times over: 12.8 ms at 2048^3 against
+// 0.97 ms here.
+template <int H>
+__global__ void k_init_blocks(Geom g) {
+    using Piece = std::conditional_t<H == 16, uint16_t, uint8_t>;
+    const uint64_t b = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= g.N >> 7) return;
+    const U4 w = philox10((uint32_t)b, (uint32_t)(b >> 32), 0xFFFFFFFEu, 0xFFFFFFFEu, g.seed);
+    const uint32_t words[4] = {w.x, w.y, w.z, w.w};
+    const uint64_t i = b << 7, plane = (uint64_t)g.L * g.L;
+    uint32_t z = (uint32_t)(i / plane);
+    const uint32_t rem = (uint32_t)(i - z * plane);
+    uint32_t y = rem / (uint32_t)g.L, x = rem - y * (uint32_t)g.L;
+    Piece *const out = reinterpret_cast<Piece *>(g.A);
+#pragma unroll
+    for (int p = 0; p < 128 / H; ++p) {
+        const uint32_t k = x / (2 * H) + (uint32_t)g.nd * (y / (2 * H) + (uint32_t)g.nd * (z / (2 * H)));
+        const uint32_t s = ((x / H) & 1u) | (((y / H) & 1u) << 1) | (((z / H) & 1u) << 2);
+        out[((uint64_t)k * 8 + s) * (H * H) + (y % H) + H * (z % H)] =
+            (Piece)(words[p * H / 32] >> (p * H % 32));
+        x += H;
+        if (x == (uint32_t)g.L) {
+            x = 0;
+            if (++y == (uint32_t)g.L) y = 0, ++z;
+        }
     }
 }
 
@@ -103,32 +137,154 @@ __global__ void k_build_faces(Geom g) {
     g.F[fw] = word;
 }
 
-// M and B of the whole lattice (each bond once: +x, +y, +z of every site).
-template <class S>
-__global__ void k_observables(Geom g) {
-    __shared__ long long shM[256], shB[256];
-    long long m = 0, b = 0;
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < g.N; i += (uint64_t)gridDim.x * blockDim.x) {
-        int x = (int)(i % g.L), y = (int)((i / g.L) % g.L), z = (int)(i / ((uint64_t)g.L * g.L));
-        int s = S::get(g, x, y, z);
-        m += s;
-        b += s * (S::get(g, x + 1 == g.L ? 0 : x + 1, y, z) + S::get(g, x, y + 1 == g.L ? 0 : y + 1, z) +
-                  S::get(g, x, y, z + 1 == g.L ? 0 : z + 1));
-    }
-    shM[threadIdx.x] = m;
-    shB[threadIdx.x] = b;
-    __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            shM[threadIdx.x] += shM[threadIdx.x + o];
-            shB[threadIdx.x] += shB[threadIdx.x + o];
+// The same for octant edges 8 and 16, a word of a face at a time: z faces are words
+// of the source octant, y faces its rows (one per plane), x faces one bit of each
+// row.  (A bit at a time with run-time divisions: 5.6 ms at 2048^3, this
+// 0.66 ms.)
+template <int H>
+__global__ void k_build_faces_rows(Geom g) {
+    constexpr uint32_t FW = H * H / 32, WP = H * H / 32, RW = 32 / H;  // words per face, per plane; rows per word
+    const uint64_t fw = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (fw >= (uint64_t)g.K * 8 * 6 * FW) return;
+    const uint64_t oct = fw / (6 * FW);
+    const uint32_t in = (uint32_t)(fw - oct * (6 * FW)), f = in / FW, j = in % FW;
+    const int a = (int)(f >> 1), side = (int)(f & 1);
+    const uint32_t *src = g.A + octant_across(g, (uint32_t)(oct >> 3), (int)(oct & 7u), a, side) * (H * WP);
+    const uint32_t e = side ? 0u : H - 1;
+    uint32_t word = 0;
+    if (a == 2) {
+        word = src[e * WP + j];
+    } else if (a == 1) {
+#pragma unroll
+        for (uint32_t r = 0; r < RW; ++r)  // row e of planes RW j, RW j + 1, ...
+            word |= ((src[(j * RW + r) * WP + e / RW] >> (H * (e % RW))) & ((1u << H) - 1u)) << (H * r);
+    } else {
+#pragma unroll
+        for (uint32_t p = 0; p < H; ++p) {  // rows 32 j .. 32 j + 31 of the octant, RW to a word
+            const uint32_t w = src[j * H + p] >> e;
+#pragma unroll
+            for (uint32_t r = 0; r < RW; ++r) word |= ((w >> (H * r)) & 1u) << (p * RW + r);
         }
-        __syncthreads();
     }
+    g.F[fw] = word;
+}
+
+// M and B of the whole lattice (each bond once: +x, +y, +z of every site): sums
+// over the workgroup, then one addition per workgroup.
+__device__ void add_observables(const Geom &g, long long m, long long b) {
+    __shared__ long long part[2][16];
+    for (int o = 32; o > 0; o >>= 1) {
+        m += __shfl_xor(m, o);
+        b += __shfl_xor(b, o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        part[0][threadIdx.x >> 6] = m;
+        part[1][threadIdx.x >> 6] = b;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        atomicAdd((unsigned long long *)&g.st->M, (unsigned long long)shM[0]);
-        atomicAdd((unsigned long long *)&g.st->B, (unsigned long long)shB[0]);
+        for (unsigned w = 1; w < blockDim.x >> 6; ++w) {
+            m += part[0][w];
+            b += part[1][w];
+        }
+        atomicAdd((unsigned long long *)&g.st->M, (unsigned long long)m);
+        atomicAdd((unsigned long long *)&g.st->B, (unsigned long long)b);
     }
+}
+
+// INT8: a wavefront per row of sites.
+__global__ void k_observables_int8(Geom g) {
+    const uint32_t L = (uint32_t)g.L, rows = L * L;
+    const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+    long long m = 0, b = 0;
+    for (uint32_t r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6; r < rows; r += waves) {
+        const uint32_t z = r / L, y = r - z * L;
+        const int8_t *row = g.spin8 + (uint64_t)r * L;
+        const int8_t *ry = g.spin8 + ((uint64_t)z * L + (y + 1 == L ? 0 : y + 1)) * L;
+        const int8_t *rz = g.spin8 + ((uint64_t)(z + 1 == L ? 0 : z + 1) * L + y) * L;
+        int rm = 0, rb = 0;  // at most L <= 4096 sites
+        for (uint32_t x = threadIdx.x & 63; x < L; x += 64) {
+            const int v = row[x];
+            rm += v;
+            rb += v * (row[x + 1 == L ? 0 : x + 1] + ry[x] + rz[x]);
+        }
+        m += rm;
+        b += rb;
+    }
+    add_observables(g, m, b);
+}
+
+// PACKED: M from the set bits, B from the bits that differ from their upper
+// neighbour's along each axis (three bonds per site, two less for each that
+// differs); the layer above an octant's last one comes from its halo copy.
+// Octant edges 8 and 16 a word at a time (a site at a time through the general
+// accessor: 62.8 ms at 2048^3 and 127 us at 256^3; this 1.1 ms and 14 us).
+template <int H>
+__global__ void k_observables_words(Geom g) {
+    constexpr uint32_t WP = H * H / 32, WO = H * WP, RW = 32 / H;  // words per plane and octant, rows per word
+    constexpr uint32_t kLast = H == 16 ? 0x80008000u : 0x80808080u;  // the last site of every row
+    const uint64_t total = (uint64_t)g.K * 8 * WO;
+    long long m = 0, b = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t oct = i / WO;
+        const uint32_t in = (uint32_t)(i % WO), z = in / WP, p = in % WP;
+        const uint32_t *A = g.A + oct * WO;
+        const uint32_t *F = g.F + oct * (6 * WP);  // a face holds as many words as a plane
+        const uint32_t w = A[in];
+        const uint32_t bits = F[WP + (z * H + p * RW) / 32] >> ((z * H + p * RW) % 32);  // x above, rows p RW ...
+        uint32_t xh = 0;
+#pragma unroll
+        for (uint32_t r = 0; r < RW; ++r) xh |= ((bits >> r) & 1u) << (H * r + H - 1);
+        const uint32_t wx = ((w >> 1) & ~kLast) | xh;
+        // y above: bit lx + H lz of slot 3
+        const uint32_t up = p + 1 < WP ? A[in + 1] : F[3 * WP + z / RW] >> (H * (z % RW));
+        const uint32_t wy = (w >> H) | (up << (32 - H));
+        const uint32_t wz = z + 1 < H ? A[in + WP] : F[5 * WP + p];
+        m += 2 * (int)__builtin_popcount(w) - 32;
+        b += 96 - 2 * (int)(__builtin_popcount(w ^ wx) + __builtin_popcount(w ^ wy) + __builtin_popcount(w ^ wz));
+    }
+    add_observables(g, m, b);
+}
+
+// Any octant edge: a row of h sites per thread, up to 32 at a time.
+__device__ __forceinline__ uint32_t bits_at(const uint32_t *w, uint64_t at, uint32_t n) {  // n <= 32 bits from bit `at`
+    const uint32_t sh = (uint32_t)(at & 31);
+    uint32_t v = w[at >> 5] >> sh;
+    if (sh + n > 32) v |= w[(at >> 5) + 1] << (32 - sh);
+    return n == 32 ? v : v & ((1u << n) - 1u);
+}
+__global__ void k_observables_rows(Geom g) {
+    const uint32_t h = (uint32_t)g.h;
+    const uint64_t total = (uint64_t)g.K * 8 * g.h2;
+    long long m = 0, b = 0;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t oct = i / g.h2;
+        const uint32_t in = (uint32_t)(i - oct * g.h2), z = in / h, y = in - z * h;
+        const uint32_t *A = g.A + oct * g.wpo, *F = g.F + oct * g.fwpo;
+        for (uint32_t x = 0; x < h; x += 32) {
+            const uint32_t n = h - x < 32 ? h - x : 32;
+            const uint32_t w = bits_at(A, (uint64_t)in * h + x, n);
+            const uint32_t next = x + n < h ? bits_at(A, (uint64_t)in * h + x + n, 1) : bits_at(F, g.h2 + in, 1);
+            const uint32_t wx = (w >> 1) | (next << (n - 1));
+            const uint32_t wy = y + 1 < h ? bits_at(A, (uint64_t)(in + 1) * h + x, n)
+                                          : bits_at(F, 3ull * g.h2 + (uint64_t)z * h + x, n);
+            const uint32_t wz = z + 1 < h ? bits_at(A, (uint64_t)(in + h) * h + x, n)
+                                          : bits_at(F, 5ull * g.h2 + (uint64_t)y * h + x, n);
+            m += 2 * (int)__builtin_popcount(w) - (int)n;
+            b += 3 * (int)n -
+                 2 * (int)(__builtin_popcount(w ^ wx) + __builtin_popcount(w ^ wy) + __builtin_popcount(w ^ wz));
+        }
+    }
+    add_observables(g, m, b);
+}
+
+// The state header, records and scratch before the spins cleared (`words` 64-bit
+// words from the start of the buffer), and the rate table written.
+__global__ void k_clear(Geom g, uint64_t words) {
+    uint64_t *p = reinterpret_cast<uint64_t *>(g.st);
+    constexpr uint64_t r0 = sizeof(DevState) / 8;  // the rates follow the header
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += (uint64_t)gridDim.x * blockDim.x)
+        p[i] = i >= r0 && i < r0 + 14 ? double_to_bits(g.r[i - r0]) : 0ull;
 }
 
 // --------------------------------------------------------------------------- cycle
@@ -305,10 +461,23 @@ __global__ void k_finalize(Geom g, uint64_t n, uint32_t obs_every) {
 }
 
 // --------------------------------------------------------------------------- host launchers
+hipError_t launch_clear(const Geom &g, size_t bytes, hipStream_t stream) {
+    const uint64_t words = bytes / 8;
+    uint64_t blocks = (words + 1023) / 1024;  // four words per thread
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)blocks), dim3(256), 0, stream, g, words);
+    return hipGetLastError();
+}
+
 hipError_t launch_init(const Geom &g, int init, hipStream_t stream) {
+    const uint64_t blocks128 = (g.N + 127) / 128;
+    const unsigned grid128 = (unsigned)((blocks128 + 255) / 256);
     if (g.layout == SPKMC_LAYOUT_INT8) {
-        uint64_t blocks128 = (g.N + 127) / 128;
-        hipLaunchKernelGGL(k_init_int8, dim3((unsigned)((blocks128 + 255) / 256)), dim3(256), 0, stream, g, init);
+        hipLaunchKernelGGL(k_init_int8, dim3(grid128), dim3(256), 0, stream, g, init);
+    } else if (init == SPKMC_INIT_RANDOM && g.h == 16) {
+        hipLaunchKernelGGL(k_init_blocks<16>, dim3(grid128), dim3(256), 0, stream, g);
+    } else if (init == SPKMC_INIT_RANDOM && g.h == 8) {
+        hipLaunchKernelGGL(k_init_blocks<8>, dim3(grid128), dim3(256), 0, stream, g);
     } else {
         uint64_t words = (uint64_t)g.K * 8 * g.wpo;
         hipLaunchKernelGGL(k_init_packed, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, stream, g, init);
@@ -319,17 +488,26 @@ hipError_t launch_init(const Geom &g, int init, hipStream_t stream) {
 hipError_t launch_faces(const Geom &g, hipStream_t stream) {
     if (g.layout != SPKMC_LAYOUT_PACKED) return hipSuccess;
     uint64_t fwords = (uint64_t)g.K * 8 * g.fwpo;
-    hipLaunchKernelGGL(k_build_faces, dim3((unsigned)((fwords + 255) / 256)), dim3(256), 0, stream, g);
+    const dim3 grid((unsigned)((fwords + 255) / 256));
+    if (g.h == 16) hipLaunchKernelGGL(k_build_faces_rows<16>, grid, dim3(256), 0, stream, g);
+    else if (g.h == 8) hipLaunchKernelGGL(k_build_faces_rows<8>, grid, dim3(256), 0, stream, g);
+    else hipLaunchKernelGGL(k_build_faces, grid, dim3(256), 0, stream, g);
     return hipGetLastError();
 }
 
+// Adds M and B of the lattice to the state header (zero before).
 hipError_t launch_observables(const Geom &g, hipStream_t stream) {
-    uint64_t blocks = (g.N + 255) / 256;
-    if (blocks > 4096) blocks = 4096;
-    if (g.layout == SPKMC_LAYOUT_INT8)
-        hipLaunchKernelGGL(k_observables<Int8Spins>, dim3((unsigned)blocks), dim3(256), 0, stream, g);
-    else
-        hipLaunchKernelGGL(k_observables<PackedSpins>, dim3((unsigned)blocks), dim3(256), 0, stream, g);
+    // items per thread: eight, or more where that many workgroups (each adds to one
+    // word of the header) would exceed 1024
+    const bool int8 = g.layout == SPKMC_LAYOUT_INT8, words = !int8 && (g.h == 8 || g.h == 16);
+    const uint64_t items = int8 ? (uint64_t)g.L * g.L * 64 : words ? g.N / 32 : g.N / (uint64_t)g.h;
+    uint64_t blocks = (items + 2047) / 2048;
+    if (blocks > 1024) blocks = 1024;
+    const dim3 grid((unsigned)blocks);
+    if (int8) hipLaunchKernelGGL(k_observables_int8, grid, dim3(256), 0, stream, g);
+    else if (g.h == 16) hipLaunchKernelGGL(k_observables_words<16>, grid, dim3(256), 0, stream, g);
+    else if (g.h == 8) hipLaunchKernelGGL(k_observables_words<8>, grid, dim3(256), 0, stream, g);
+    else hipLaunchKernelGGL(k_observables_rows, grid, dim3(256), 0, stream, g);
     return hipGetLastError();
 }
 

@@ -274,9 +274,7 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     if (c->engine == SPKMC_ENGINE_CYCLE) (void)resident_configure(g, c->res);
 
     hipError_t e;
-    if ((e = hipMemsetAsync(c->dev, 0, lp.off_spin, c->stream)) != hipSuccess) return hip_fail(c, e, "hipMemsetAsync");
-    if ((e = hipMemcpyAsync(c->dev + lp.off_rates, g.r, sizeof g.r, hipMemcpyHostToDevice, c->stream)) != hipSuccess)
-        return hip_fail(c, e, "hipMemcpyAsync(rates)");
+    if ((e = launch_clear(g, lp.off_spin, c->stream)) != hipSuccess) return hip_fail(c, e, "clear kernel");
     if ((e = launch_init(g, p->init, c->stream)) != hipSuccess) return hip_fail(c, e, "init kernel");
     if ((e = launch_faces(g, c->stream)) != hipSuccess) return hip_fail(c, e, "face kernel");
     if ((e = launch_observables(g, c->stream)) != hipSuccess) return hip_fail(c, e, "observables kernel");

@@ -11,6 +11,7 @@ namespace spkmc {
 hipError_t launch_clear(const Geom &g, size_t bytes, hipStream_t stream);
 hipError_t launch_init(const Geom &g, int init, hipStream_t stream);
 hipError_t launch_faces(const Geom &g, hipStream_t stream);
+hipError_t launch_reset_observables(const Geom &g, hipStream_t stream);  // M = B = 0
 hipError_t launch_observables(const Geom &g, hipStream_t stream);
 // slab: the per-cycle slab kernels (their counts binned by launch_slab_bin first)
 hipError_t launch_cycle(const Geom &g, uint64_t n, uint32_t obs_every, hipStream_t stream, bool slab);

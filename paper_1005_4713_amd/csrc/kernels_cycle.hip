@@ -278,6 +278,10 @@ __global__ void k_observables_rows(Geom g) {
     add_observables(g, m, b);
 }
 
+__global__ void k_reset_observables(Geom g) {
+    if (threadIdx.x == 0) g.st->M = g.st->B = 0;
+}
+
 // The state header, records and scratch before the spins cleared (`words` 64-bit
 // words from the start of the buffer), and the rate table written.
 __global__ void k_clear(Geom g, uint64_t words) {
@@ -492,6 +496,11 @@ hipError_t launch_faces(const Geom &g, hipStream_t stream) {
     if (g.h == 16) hipLaunchKernelGGL(k_build_faces_rows<16>, grid, dim3(256), 0, stream, g);
     else if (g.h == 8) hipLaunchKernelGGL(k_build_faces_rows<8>, grid, dim3(256), 0, stream, g);
     else hipLaunchKernelGGL(k_build_faces, grid, dim3(256), 0, stream, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_reset_observables(const Geom &g, hipStream_t stream) {
+    hipLaunchKernelGGL(k_reset_observables, dim3(1), dim3(64), 0, stream, g);
     return hipGetLastError();
 }
 

@@ -37,3 +37,25 @@ def test_start(spkmc, L, d, layout, init):
     want = oracle.Sim(L=L, d=d, init=spkmc.INITS[init], seed=(1 << 40) + 7).spins()
     assert np.array_equal(sim.spins(), want)
     assert sim.state() == (0, 0, 0, 0.0) + _observables(want, L)
+
+
+@pytest.mark.parametrize("L,d,layout", SHAPES)
+def test_spins_set_and_read(spkmc, L, d, layout):
+    """Any spins come back as they were set, with their M and B; what is not +1 or -1
+    is refused, wherever it is, and changes nothing."""
+    print("case set spins", L, d, layout, flush=True)
+    sim = spkmc.Sim(L, d, layout=layout, seed=3)
+    want = np.random.default_rng(L * d).choice(np.array([-1, 1], dtype=np.int8), L ** 3)
+    sim.set_spins(want)
+    assert np.array_equal(sim.spins(), want)
+    assert sim.state()[4:] == _observables(want, L)
+    for bad in (0, 2, -2, 127, -128, -127):
+        spins = np.ones(L ** 3, dtype=np.int8)
+        spins[(bad * 37) % L ** 3] = bad
+        with pytest.raises(spkmc.SpkmcError):
+            sim.set_spins(spins)
+    assert np.array_equal(sim.spins(), want)
+    assert sim.state()[4:] == _observables(want, L)
+    # the halo copies: a cycle from these spins ends with the M and B of its spins
+    sim.run(3)
+    assert sim.state()[4:] == _observables(sim.spins(), L)

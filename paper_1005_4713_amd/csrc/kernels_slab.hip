@@ -954,7 +954,7 @@ hipError_t launch_slab(const Geom &g, uint64_t n0, uint64_t ncycles, uint32_t ob
     R.G = (uint32_t)grid;
     R.pad = 0;
     void *args[] = {&R};
-    return hipLaunchCooperativeKernel(slab_kernel(g), dim3(grid), dim3(kSlabBlock), args, 0, stream);
+    return launch_resident_grid(slab_kernel(g), grid, kSlabBlock, args, stream);
 }
 
 }  // namespace spkmc

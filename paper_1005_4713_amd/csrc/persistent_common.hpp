@@ -826,6 +826,7 @@ struct RowsGeometry {
 // The sync scratch of a persistent launch of G workgroups (kernels_persistent.hip),
 // and its set-up before a launch starting at cycle n0.
 PersistScratch scratch_of(const Geom &g, int G);
+hipError_t launch_resident_grid(const void *kern, int grid, int block, void **args, hipStream_t stream);
 hipError_t launch_persistent_prep(const PersistScratch &xs, uint32_t G, uint64_t n0, hipStream_t stream);
 
 // The neighbour workgroups of this workgroup per direction, from the bitmap

@@ -5,8 +5,8 @@
 // What bounds it: a latency chain per cycle (LDS reads, barriers and, with more
 // than one workgroup, the R_max exchange); it reads nothing from memory but
 // other workgroups' words.  Per cycle, records included, against the three
-// launches per cycle it replaces: L = 16, d = 8 (one workgroup) 3.7 us against
-// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 7.2 us against 77, of
+// launches per cycle it replaces: L = 16, d = 8 (one workgroup) 2.7 us against
+// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 7.0 us against 77, of
 // which binning took 49 (a workgroup per line of 64 sites); L = 72, d = 8, two
 // colours 6.5 us against 58.
 //
@@ -45,9 +45,9 @@ struct ResidentHead {
     double r[16];                 // rate of each byte value
     unsigned long long wmax[16];  // per wavefront: its largest line
     unsigned long long stat[2];   // this workgroup's counters of cycle n (bank n & 1)
+    double lnu[4];                // -ln u of the clock step of cycle n (place n & 3)
     double rmax;
-    double lnu;   // -ln u of the next cycle's clock step
-    int colour;   // the next cycle's colour
+    int colour[4];                // colour of cycle n (place n & 3)
     int abort;
 };
 constexpr uint32_t kHeadBytes = 512;
@@ -127,11 +127,15 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
     ResidentHead &sh = *reinterpret_cast<ResidentHead *>(lds_raw);
     uint32_t *const cnt = reinterpret_cast<uint32_t *>(lds_raw) + kHeadBytes / 4;  // [domain][octant][8]
     uint32_t *const nbr = cnt + A.D * 64;                                          // [domain][6]
-    uint32_t *const cls = nbr + A.D * 6;                                           // [domain][octant][ow]
+    uint32_t *const org = nbr + A.D * 6;                                           // [domain]
+    uint32_t *const cls = org + A.D;                                               // [domain][octant][ow]
+    // one workgroup: the lines' numbers, drawn a cycle ahead [n & 1][line]
+    uint4 *const drawn = lds_raw + (kHeadBytes / 4 + A.D * (71 + 8 * ow) + 3) / 4;
     const int tid = threadIdx.x, nthr = blockDim.x, lane = tid & 63, wave = tid >> 6, nwaves = nthr >> 6;
     const int l = tid & (GS - 1);
     const uint32_t group = (uint32_t)tid / GS, groups = (uint32_t)nthr / GS;
-    const bool svc = wave == nwaves - 1;  // records, the clock and the next cycle's draw
+    const bool svc = wave == nwaves - 1;  // records and the clock
+    const bool drw = wave == nwaves - 2;  // the draws of the coming cycles
     DevState *const st = g.st;
     const uint64_t n0 = A.n0, n_end = A.n0 + A.ncycles;
     const bool rmax_all = (g.variant & SPKMC_VARIANT_RMAX_ALL) != 0;
@@ -140,6 +144,7 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
 
     // --- set-up: tables, then every own site's byte from the spins and halos
     if (tid < 16) sh.r[tid] = tid < 7 ? g.r[6 - tid] : tid >= 8 && tid < 15 ? g.r[tid - 1] : 0.0;
+    if (tid < 16) sh.wmax[tid] = 0;  // of wavefronts this launch has not
     if (tid == 0) {
         sh.abort = 0;
         sh.stat[0] = sh.stat[1] = 0;
@@ -150,6 +155,10 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         int kc[3] = {c.kx, c.ky, c.kz};
         kc[a] = (dir & 1) ? wrapp(kc[a], g.nd) : wrapm(kc[a], g.nd);
         nbr[i] = dindex(kc[0], kc[1], kc[2], g.nd);
+    }
+    for (uint32_t i = (uint32_t)tid; i < nown; i += nthr) {  // the domain's first site in linear order
+        const DomainCoord c = dcoord(kbase + i, g.nd);
+        org[i] = (uint32_t)g.d * ((uint32_t)c.kx + (uint32_t)g.L * ((uint32_t)c.ky + (uint32_t)g.L * (uint32_t)c.kz));
     }
     for (uint32_t i = (uint32_t)tid; i < nown * 8 * ow; i += nthr) {
         const uint32_t oct = i / ow, k = kbase + (oct >> 3);
@@ -261,13 +270,13 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         return a;
     };
 
-    // the record keeper's totals since launch start (workgroup 0, service wavefront:
-    // each lane sums the workgroups it reads)
+    // the record keeper's totals since launch start (workgroup 0, service wavefront)
     long long totF = 0, totU = 0, totA = 0;
     const bool keeper = gid == 0 && svc;
     double t = 0.0;
     uint64_t fired0 = 0, nulls0 = 0, recs = 0, next_rec = ~0ull;
     int64_t M0 = 0, B0 = 0;
+    uint32_t ring = 0;  // the next record's place: recs mod rec_cap
     if (keeper) {
         fired0 = st->fired;
         nulls0 = st->nulls;
@@ -275,55 +284,52 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         B0 = st->B;
         t = st->t;
         recs = st->rec_count;
+        if (g.rec_cap) ring = (uint32_t)(recs % g.rec_cap);
         if (A.obs_every) next_rec = (n0 / A.obs_every + 1) * A.obs_every;
     }
-    auto add_stat = [&](unsigned long long v) {
-        totF += (long long)(v & 0xFFFFFu);
-        totU += (long long)((v >> 20) & 0xFFFFFu);
-        totA += (long long)((v >> 40) & 0x7FFFFFu);
-    };
-    // counters of cycle m into the totals (every workgroup has finished it, or is about to)
+    // counters of cycle m into the totals (every workgroup has finished it, or is about
+    // to); a whole cycle's counters fit the packed fields (fewer than 2^20 lines)
     auto gather = [&](uint64_t m) {
+        unsigned long long sum = 0;
         if (G == 1) {
-            if (lane == 0) add_stat(sh.stat[m & 1]);
-            return;
-        }
-        const unsigned long long gen = ((m >> 1) & 1) << 63;
-        for (uint32_t w = (uint32_t)lane; w < G; w += 64) {
-            const uint64_t *p = A.part + (m & 1) * (uint64_t)G + w;
-            unsigned long long v = ld64(p);
-            if ((v & kGenBit) != gen) {
-                const uint64_t start = now_ticks();
-                while (((v = ld64(p)) & kGenBit) != gen) {
-                    __builtin_amdgcn_s_sleep(1);
-                    if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
-                        atomicOr(&st->error, kErrFlagTimeout);
-                        sh.abort = 1;
-                        return;
+            sum = sh.stat[m & 1];
+        } else {
+            const unsigned long long gen = ((m >> 1) & 1) << 63;
+            for (uint32_t w = (uint32_t)lane; w < G; w += 64) {
+                const uint64_t *p = A.part + (m & 1) * (uint64_t)G + w;
+                unsigned long long v = ld64(p);
+                if ((v & kGenBit) != gen) {
+                    const uint64_t start = now_ticks();
+                    while (((v = ld64(p)) & kGenBit) != gen) {
+                        __builtin_amdgcn_s_sleep(1);
+                        if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
+                            atomicOr(&st->error, kErrFlagTimeout);
+                            sh.abort = 1;
+                            break;
+                        }
                     }
                 }
+                sum += v & ~kGenBit;
             }
-            add_stat(v);
+            for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
         }
+        totF += (long long)(sum & 0xFFFFFu);
+        totU += (long long)((sum >> 20) & 0xFFFFFu);
+        totA += (long long)((sum >> 40) & 0x7FFFFFu);
     };
     // the state after `cyc` cycles: the ring record, or at the end the counters
     auto keep = [&](uint64_t cyc, bool record, bool final) {
-        long long F = totF, U = totU, Al = totA;
-        for (int o = 32; o > 0; o >>= 1) {
-            F += __shfl_xor(F, o);
-            U += __shfl_xor(U, o);
-            Al += __shfl_xor(Al, o);
-        }
         if (lane != 0) return;
         spkmc_record r;
         r.cycle = cyc;
-        r.fired = fired0 + (uint64_t)F;
-        r.nulls = nulls0 + (uint64_t)NL * (cyc - n0) - (uint64_t)F;
+        r.fired = fired0 + (uint64_t)totF;
+        r.nulls = nulls0 + (uint64_t)NL * (cyc - n0) - (uint64_t)totF;
         r.t = t;
-        r.M = M0 + 2 * F - 4 * U;   // an up spin takes 2 from M, a down spin adds 2
-        r.B = B0 + 12 * F - 4 * Al;  // six bonds, `aligned` of them with the old spin
+        r.M = M0 + 2 * totF - 4 * totU;   // an up spin takes 2 from M, a down spin adds 2
+        r.B = B0 + 12 * totF - 4 * totA;  // six bonds, `aligned` of them with the old spin
         if (record) {
-            g.rec[recs % g.rec_cap] = r;
+            g.rec[ring] = r;
+            ring = ring + 1 == g.rec_cap ? 0 : ring + 1;
             recs += 1;
         }
         if (final) {
@@ -337,11 +343,31 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         }
     };
 
-    const CycleDraw cd0 = cycle_draw(g.seed, n0, lpd == 4);
-    int s = cd0.colour, prev = -1;
-    double lnu = svc ? -log(cd0.ut) : 0.0;
+    auto draw = [&](uint64_t n, int colour, uint32_t f) {
+        const uint32_t line = lbase + f;
+        return philox10((uint32_t)n, (uint32_t)(n >> 32), lpd == 1 ? line : line >> 2, (uint32_t)line_oct(f, colour),
+                        g.seed);
+    };
+    // one workgroup: the numbers of every line for cycle n (with more, each group draws
+    // its own while the maxima travel)
+    auto draw_lines = [&](uint64_t n, int colour) {
+        for (uint32_t f = (uint32_t)lane; f < nl; f += 64) {
+            const U4 w = draw(n, colour, f);
+            drawn[(n & 1) * nl + f] = uint4{w.x, w.y, w.z, w.w};
+        }
+    };
+    int s = 0, prev = -1;
+    if (drw) {
+        if (lane < 2) {
+            const CycleDraw cd = cycle_draw(g.seed, n0 + (uint64_t)lane, lpd == 4);
+            sh.colour[(n0 + (uint64_t)lane) & 3] = s = cd.colour;
+            sh.lnu[(n0 + (uint64_t)lane) & 3] = -log(cd.ut);
+        }
+        if (G == 1) draw_lines(n0, __builtin_amdgcn_readfirstlane(s));
+    }
     const bool one = nl <= groups;  // a single round of lines: sums and draws stay in registers
     __syncthreads();
+    s = sh.colour[n0 & 3];
 
     for (uint64_t n = n0; n < n_end; ++n) {
         // --- step 6: events of the previous cycle in other workgroups' domains, now where
@@ -377,10 +403,6 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         __syncthreads();
         const uint64_t gen = ((n >> 1) & 1) << 63;
         U4 dw{};
-        auto draw = [&](uint32_t f) {
-            const uint32_t line = lbase + f;
-            return philox10((uint32_t)n, (uint32_t)(n >> 32), lpd == 1 ? line : line >> 2, (uint32_t)line_oct(f, s), g.seed);
-        };
         if (G > 1 && wave == 0) {
             // publish, then poll every workgroup's slot (the fixed bound exchanges zeros:
             // the exchange also keeps the workgroups within a cycle of one another)
@@ -420,12 +442,14 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             best = wave_max_nonneg(best);
             if (lane == 63) sh.rmax = best;
         }
-        if (svc) {
+        if (drw) {
+            if (G == 1) draw_lines(n + 1, sh.colour[(n + 1) & 3]);
             if (lane == 0) {
-                const CycleDraw nd = cycle_draw(g.seed, n + 1, lpd == 4);
-                sh.colour = nd.colour;
-                sh.lnu = -log(nd.ut);
+                const CycleDraw cd = cycle_draw(g.seed, n + 2, lpd == 4);
+                sh.colour[(n + 2) & 3] = cd.colour;
+                sh.lnu[(n + 2) & 3] = -log(cd.ut);
             }
+        } else if (svc) {
             if (gid == 0 && n > n0) {
                 gather(n - 1);
                 if (n == next_rec) {
@@ -435,9 +459,9 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
                 if (G == 1 && lane == 0) sh.stat[(n - 1) & 1] = 0;
             }
         } else if (wave != 0) {
-            if (pending) apply_events(n - 1, prev, (uint32_t)tid - 64, (uint32_t)nthr - 128);
+            if (pending) apply_events(n - 1, prev, (uint32_t)tid - 64, (uint32_t)nthr - 192);
         }
-        if (one) dw = draw(group < nl ? group : 0);
+        if (G > 1 && one) dw = draw(n, s, group < nl ? group : 0);
         if (G > 1) {
             __syncthreads();
             if (sh.abort) break;
@@ -448,9 +472,14 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         } else if (G > 1) {
             Rmax = sh.rmax;
         } else {
-            uint64_t b = 0;
-            for (int w = 0; w < nwaves; ++w) b = sh.wmax[w] > b ? sh.wmax[w] : b;
-            Rmax = bits_to_double(b);
+            double v = bits_to_double(sh.wmax[l & 15]);
+            v = fmax(v, dpp_f64<kRowShr1, 0xF>(v));
+            v = fmax(v, dpp_f64<kRowShr2, 0xF>(v));
+            v = fmax(v, dpp_f64<kRowShr4, 0xF>(v));
+            v = fmax(v, dpp_f64<kRowShr8, 0xF>(v));  // lane 15 of each row: the largest of 16
+            const uint64_t b = double_to_bits(v);
+            Rmax = bits_to_double(((uint64_t)bcast<kRowBcast + 15>((uint32_t)(b >> 32)) << 32) |
+                                  bcast<kRowBcast + 15>((uint32_t)b));
         }
 
         // --- steps 3, 4 and 4b, and the flips
@@ -461,10 +490,13 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             const uint32_t ld = lpd == 1 ? fc : fc >> 2;
             const int o = line_oct(fc, s);
             const uint32_t oct = ld * 8 + (uint32_t)o;
-            if (!one) {
-                dw = draw(fc);
-                (void)sums(oct, acc);
+            if (G == 1) {
+                const uint4 w = drawn[(n & 1) * nl + fc];
+                dw = U4{w.x, w.y, w.z, w.w};
+            } else if (!one) {
+                dw = draw(n, s, fc);
             }
+            if (!one) (void)sums(oct, acc);
             const double target = unit53(dw.x, dw.y) * Rmax;
             int cs = -1;
 #pragma unroll
@@ -531,11 +563,9 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             } else if (l == 8) {
                 atomicAdd(&sh.stat[n & 1], stat_of(cs));
                 if (g.layout == SPKMC_LAYOUT_INT8) {
-                    const DomainCoord dc = dcoord(kbase + ld, g.nd);
-                    const uint32_t X = (uint32_t)(dc.kx * g.d + (o & 1) * h + sc.c[0]);
-                    const uint32_t Y = (uint32_t)(dc.ky * g.d + ((o >> 1) & 1) * h + sc.c[1]);
-                    const uint32_t Z = (uint32_t)(dc.kz * g.d + ((o >> 2) & 1) * h + sc.c[2]);
-                    g.spin8[X + (uint32_t)g.L * (Y + (uint32_t)g.L * Z)] = (int8_t)(up ? -1 : 1);
+                    const uint32_t X = (uint32_t)((o & 1) * h + sc.c[0]), Y = (uint32_t)(((o >> 1) & 1) * h + sc.c[1]);
+                    const uint32_t Z = (uint32_t)(((o >> 2) & 1) * h + sc.c[2]);
+                    g.spin8[org[ld] + X + (uint32_t)g.L * (Y + (uint32_t)g.L * Z)] = (int8_t)(up ? -1 : 1);
                 } else {
                     flip_word(g.A + ((uint64_t)(kbase + ld) * 8 + (uint64_t)o) * g.wpo + (q >> 5), 1u << (q & 31));
                 }
@@ -552,13 +582,10 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             }
         }
         // --- step 5, in the record keeper's wavefront (the others need no clock)
-        if (svc) {
-            t = t + lnu / (clock_s * Rmax);
-            lnu = sh.lnu;
-        }
+        if (svc) t = t + sh.lnu[n & 3] / (clock_s * Rmax);
         prev = s;
         __syncthreads();
-        s = sh.colour;  // next written after the coming barrier
+        s = sh.colour[(n + 1) & 3];
         if (G > 1 && tid == 0) {
             st64(A.part + (n & 1) * (uint64_t)G + gid, sh.stat[n & 1] | gen);
             sh.stat[n & 1] = 0;
@@ -603,16 +630,17 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
         hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
         return false;
     const uint32_t ow = (g.h3 + 3) / 4;
-    const uint64_t per_domain = 64 * 4 + 6 * 4 + 8ull * ow * 4;
+    const uint64_t per_domain = 64 * 4 + 6 * 4 + 4 + 8ull * ow * 4;
     const uint64_t room = ((uint64_t)lds - kHeadBytes) / per_domain;  // domains one workgroup holds
     if (room == 0) return false;
     const int gs = ow <= 128 ? 16 : 64;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
+    if (lines >= (1u << 20)) return false;  // a cycle's packed counters
     // one workgroup while its wavefronts take the lines in a few rounds (no exchange);
     // else as many as give each a round of kLinesPerWg lines, up to one per CU
     uint64_t G = 1;
-    if (g.K > room || lines * gs > 4096) {
-        const uint64_t per_wg = gs == 16 ? kResidentLines : 15;  // 15 groups of 64 lanes and the service wavefront
+    if (g.K * per_domain + 32 * lines + 64 > (uint64_t)lds - kHeadBytes || lines * gs > 4096) {
+        const uint64_t per_wg = gs == 16 ? kResidentLines : 14;  // 14 groups of 64 lanes and the service wavefronts
         G = (lines + per_wg - 1) / per_wg;
         const uint64_t need = (g.K + room - 1) / room;
         G = G < need ? need : G;
@@ -624,13 +652,14 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     if (D > room) return false;
     G = (g.K + D - 1) / D;
     uint64_t thr = D * g.lpd * gs;
-    thr = (thr + 63) / 64 * 64 + 64;  // a service wavefront beside the lines'
-    thr = thr < 192 ? 192 : thr > 1024 ? 1024 : thr;
+    thr = (thr + 63) / 64 * 64 + 128;  // two service wavefronts beside the lines'
+    thr = thr < 256 ? 256 : thr > 1024 ? 1024 : thr;
     out.G = (int)G;
     out.D = (int)D;
     out.gs = gs;
     out.block = (int)thr;
     out.lds = (size_t)(kHeadBytes + D * per_domain);
+    if (G == 1) out.lds += (size_t)(32 * lines + 32);  // the lines' numbers, two cycles of them
     void *kern = resident_kernel(gs);
     (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out.lds);
     int occ = 0;

@@ -9,7 +9,7 @@
 //              null event last (steps 3, 4, 4b), canonical-order prefix select
 //              of the site with wavefront ballots, flip (step 6 is the kernel
 //              boundary);
-//   k_finalize one thread: clock (step 5), counters, observation record.
+//   k_finalize one wavefront: clock (step 5), counters, observation record.
 // These kernels are generic over the spin layout and serve as the reference
 // launch shape for the persistent engine.
 #include <type_traits>
@@ -361,7 +361,7 @@ __global__ void k_bin(Geom g, uint64_t n) {
         if (Rk > wmax) wmax = Rk;
     }
     if (threadIdx.x == 0 && !(g.variant & SPKMC_VARIANT_RMAX_BOUND) && blockIdx.x < lines)
-        atomicMax((unsigned long long *)&g.st->rmax[0], (unsigned long long)double_to_bits(wmax));
+        raise_rmax(g, double_to_bits(wmax));
 }
 
 // Steps 3, 4, 4b and the flip.  One 64-lane wavefront per frequency line, four
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(256) k_select(Geom g, uint64_t n) {
     int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint32_t lines = g.K * g.lpd;  // < 2^31 (checked at set-up)
     const CycleDraw cd = cycle_draw(g.seed, n, g.lpd == 4);
-    const double Rmax = (g.variant & SPKMC_VARIANT_RMAX_BOUND) ? g.rbound : bits_to_double(g.st->rmax[0]);
+    const double Rmax = cycle_rmax(g);
     long long fired = 0, dM = 0, dB = 0;
     for (uint32_t f = blockIdx.x * 4 + wave; f < lines; f += gridDim.x * 4) {
         uint32_t k;
@@ -453,15 +453,13 @@ __global__ void __launch_bounds__(256) k_select(Geom g, uint64_t n) {
             m += part[w][1];
             b += part[w][2];
         }
-        if (f) atomicAdd((unsigned long long *)&g.st->acc_fired[0], (unsigned long long)f);
-        if (m) atomicAdd((unsigned long long *)&g.st->acc_dM[0], (unsigned long long)m);
-        if (b) atomicAdd((unsigned long long *)&g.st->acc_dB[0], (unsigned long long)b);
+        add_counters(g, f, m, b);
     }
 }
 
 // Step 5 and the bookkeeping of cycle n.
 __global__ void k_finalize(Geom g, uint64_t n, uint32_t obs_every) {
-    if (threadIdx.x == 0) finalize_cycle(g, n, obs_every);
+    finalize_cycle(g, n, obs_every);
 }
 
 // --------------------------------------------------------------------------- host launchers

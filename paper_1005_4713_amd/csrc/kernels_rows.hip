@@ -14,7 +14,7 @@ namespace spkmc {
 // The per-cycle engine's row kernels (PACKED, octant edge 8 or 16): one cycle in
 // two launches, for lattices of any size.  k_rows_bin bins every line with the
 // persistent kernel's rows and passes (step 1) and takes the maximum (step 2)
-// into st->rmax[0]; k_rows_select derives the class planes again, draws,
+// into the cycle's R_max; k_rows_select derives the class planes again, draws,
 // selects and flips (steps 3, 4, 4b; step 6 is the launch boundary); the
 // per-cycle k_finalize keeps the clock, the counters and the records (step 5).
 constexpr int kRowsPasses = 4;  // passes of the row kernels (128 or 256 lines per workgroup)
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows_bin(Geom g, uint64_t n) {
     }
     __syncthreads();
     if (tid == 0 && rg.nvalid && !(g.variant & SPKMC_VARIANT_RMAX_BOUND))
-        atomicMax((unsigned long long *)&g.st->rmax[0], sh.wmax);
+        raise_rmax(g, sh.wmax);
 }
 
 template <int H, int BLOCK, int LPD, int PASSES>
@@ -92,7 +92,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows_select(Geom g, uint64_t n) {
     const RG rg(g);
     const int tid = threadIdx.x, row = tid >> 4, l = tid & 15;
     const int s = cycle_draw(g.seed, n, rg.lpd == 4).colour;
-    const double Rmax = (g.variant & SPKMC_VARIANT_RMAX_BOUND) ? g.rbound : bits_to_double(g.st->rmax[0]);
+    const double Rmax = cycle_rmax(g);
     rg.neighbours(sh.nbdom);
     if (l < 8) sh.zbuf[row][48 + l] = 0;
     // the counts of every line and their running sums, in the order of step 1
@@ -161,9 +161,7 @@ __global__ void __launch_bounds__(BLOCK) k_rows_select(Geom g, uint64_t n) {
             dM += sh.red[1][w];
             dB += sh.red[2][w];
         }
-        if (F) atomicAdd((unsigned long long *)&g.st->acc_fired[0], (unsigned long long)F);
-        if (dM) atomicAdd((unsigned long long *)&g.st->acc_dM[0], (unsigned long long)dM);
-        if (dB) atomicAdd((unsigned long long *)&g.st->acc_dB[0], (unsigned long long)dB);
+        add_counters(g, F, dM, dB);
     }
 }
 

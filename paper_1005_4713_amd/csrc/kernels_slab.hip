@@ -697,26 +697,35 @@ __global__ void __launch_bounds__(kSlabBlock) k_slab(Replica R) {
 // Per-cycle slab kernels (PACKED, octant edge 16, eight colours): one cycle in
 // two launches from the slab counts, for lattices of any size.  k_srows_max
 // takes every line's frequency line (every octant's with the all-octant R_max)
-// from its count words and the largest into st->rmax[0]; k_srows_select stages
+// from its count words and the largest into the cycle's R_max; k_srows_select stages
 // each line's counts, octant and halo in LDS, draws, selects in one slab and
-// flips (the class moves as in the slab engine).  The counts are binned once per
-// run by k_slab_bin; kernel boundaries order every read after the writes it needs.
+// flips (the class moves as in the slab engine).  The counts are binned by
+// k_slab_bin before the first run after anything else changed the spins; kernel
+// boundaries order every read after the writes it needs.
 // ---------------------------------------------------------------------------
+// 64 lines to a workgroup: two workgroups' LDS (62 KB each) fit a CU, so that one's
+// loads overlap the other's selection, and its flips fill all four wavefronts.  20
+// cycles of 2048^3 on one box: 3.74 ms; 512 threads and 64 lines 3.88, 128 lines
+// 4.15, 256 threads and 32 lines 4.70.
+constexpr int kSrowsBlock = 256, kSrowsPasses = 4;
+constexpr uint32_t kSrowsLines = kSrowsBlock / 16 * kSrowsPasses;  // lines of one k_srows_select workgroup
 struct SrowsShared {
-    alignas(16) uint32_t oct[kSlabDomains][kOctLds];
-    uint32_t sc[kSlabDomains][kSlabWords];
-    double acc[kSlabDomains][14];
-    uint32_t nbdom[kSlabDomains][6];
-    uint32_t dco[kSlabDomains];
-    uint32_t selq[kSlabDomains];
-    alignas(16) uint32_t zbuf[kSlabRows][kRowHalo];
-    unsigned long long wmax;
+    alignas(16) uint32_t oct[kSrowsLines][kOctLds];
+    uint32_t sc[kSrowsLines][kSlabWords];
+    double acc[kSrowsLines][14];
+    uint32_t nbdom[kSrowsLines][6];
+    uint32_t dco[kSrowsLines];
+    uint32_t selq[kSrowsLines];
     long long red[3][16];
+};
+struct SlabBinShared {
+    uint32_t nbdom[kSlabDomains][6];
+    alignas(16) uint32_t zbuf[kSlabRows][kRowHalo];
 };
 
 // The slab counts of every octant of 128 domains per workgroup, from the spins.
 __global__ void __launch_bounds__(kSlabBlock) k_slab_bin(Geom g) {
-    __shared__ SrowsShared sh;
+    __shared__ SlabBinShared sh;
     const int tid = threadIdx.x, row = tid >> 4, l = tid & 15;
     const uint32_t kbase = blockIdx.x * kSlabDomains;
     const uint32_t nvalid = kbase >= g.K ? 0u : (g.K - kbase < kSlabDomains ? g.K - kbase : kSlabDomains);
@@ -735,7 +744,7 @@ __global__ void __launch_bounds__(kSlabBlock) k_slab_bin(Geom g) {
 }
 
 // Every line's frequency line from its count words (with the all-octant R_max:
-// every octant of every domain), the largest into st->rmax[0].  One thread per
+// every octant of every domain), the largest into the cycle's R_max.  One thread per
 // line (or octant).
 template <int LPD>
 __global__ void __launch_bounds__(256) k_srows_max(Geom g, uint64_t n) {
@@ -767,28 +776,23 @@ __global__ void __launch_bounds__(256) k_srows_max(Geom g, uint64_t n) {
         atomicMax(&wmax, (unsigned long long)double_to_bits(line_total(cnt, g.r)));
     }
     __syncthreads();
-    if (tid == 0 && wmax) atomicMax((unsigned long long *)&g.st->rmax[0], wmax);
+    if (tid == 0 && wmax) raise_rmax(g, wmax);
 }
 
 template <int LPD>
-__global__ void __launch_bounds__(kSlabBlock) k_srows_select(Geom g, uint64_t n) {
+__global__ void __launch_bounds__(kSrowsBlock) k_srows_select(Geom g, uint64_t n) {
     __shared__ SrowsShared sh;
-    using RG = RowsGeometry<16, kSlabBlock, LPD, kSlabPasses>;
+    using RG = RowsGeometry<16, kSrowsBlock, LPD, kSrowsPasses>;
     constexpr int rows = RG::rows, P = RG::P;
     constexpr uint32_t D = RG::D;
     const RG rg(g);
     const int tid = threadIdx.x, row = tid >> 4, l = tid & 15;
     const int s = cycle_draw(g.seed, n, rg.lpd == 4).colour;
-    const double Rmax = (g.variant & SPKMC_VARIANT_RMAX_BOUND) ? g.rbound : bits_to_double(g.st->rmax[0]);
-    rg.neighbours(sh.nbdom);
-    for (uint32_t i = tid; i < rg.nvalid; i += kSlabBlock) {
-        const DomainCoord c = dcoord(rg.dom(rg.kbase + i), g.nd);
-        sh.dco[i] = (uint32_t)c.kx | ((uint32_t)c.ky << 10) | ((uint32_t)c.kz << 20);
-    }
-    __syncthreads();
-    // each line's counts (lane c: class c) and its octant and halo, into LDS
+    // each line's counts (lane c: class c) and its octant and halo go out first
     const int endSC = (int)((uint64_t)g.K * 8u * kSlabWords * 4u);
     const __amdgpu_buffer_rsrc_t SC = __builtin_amdgcn_make_buffer_rsrc((void *)g.sc, (short)0, endSC, 0x00020000);
+    Raw<16> raw[P];
+    uint32_t scw[P][2];
 #pragma unroll
     for (int pp = 0; pp < P; ++pp) {
         const uint32_t ld = (uint32_t)(pp * rows + row);
@@ -796,20 +800,38 @@ __global__ void __launch_bounds__(kSlabBlock) k_srows_select(Geom g, uint64_t n)
         const uint32_t k = rg.dom(rg.kbase + ld), o = (uint32_t)rg.oct(rg.kbase + ld, s);
         const int off = valid && l < 14 ? (int)(((k * 8u + o) * kSlabWords + 2u * (uint32_t)l) * 4u) : endSC;
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(SC, off, 0, kCoherent);
-        Raw<16> raw;
-        load_octant<16>(g, k, (int)o, valid, l, sh.nbdom[valid ? ld : 0], raw);
-        if (l < 14) {
-            sh.sc[ld][2 * l] = v[0];
-            sh.sc[ld][2 * l + 1] = v[1];
-        }
-        uint32_t *oc = sh.oct[ld];
+        scw[pp][0] = v[0];
+        scw[pp][1] = v[1];
+    }
 #pragma unroll
-        for (int w = 0; w < 8; ++w) oc[8 * l + w] = raw.W[w];
-        if (l < 12) *reinterpret_cast<uint4 *>(oc + kFxm + 4 * l) = uint4{raw.F[0], raw.F[1], raw.F[2], raw.F[3]};
+    for (int pp = 0; pp < P; ++pp) {
+        const uint32_t ld = (uint32_t)(pp * rows + row);
+        load_octant<16>(g, rg.dom(rg.kbase + ld), rg.oct(rg.kbase + ld, s), ld < rg.nvalid, l, nullptr, raw[pp]);
+    }
+    // while they travel: the maximum, the neighbour tables and the lines' numbers
+    // (lane pp of each row draws for the row's line of pass pp)
+    const double Rmax = cycle_rmax(g);
+    rg.neighbours(sh.nbdom);
+    for (uint32_t i = tid; i < rg.nvalid; i += kSrowsBlock) {
+        const DomainCoord c = dcoord(rg.dom(rg.kbase + i), g.nd);
+        sh.dco[i] = (uint32_t)c.kx | ((uint32_t)c.ky << 10) | ((uint32_t)c.kz << 20);
+    }
+    U4 dw;
+    {
+        const uint32_t kd = rg.kbase + (uint32_t)((l < P ? l : 0) * rows + row);
+        dw = philox10((uint32_t)n, (uint32_t)(n >> 32), rg.dom(kd), (uint32_t)rg.oct(kd, s), g.seed);
+    }
+#pragma unroll
+    for (int pp = 0; pp < P; ++pp) {
+        const uint32_t ld = (uint32_t)(pp * rows + row);
+        if (l < 14) {
+            sh.sc[ld][2 * l] = scw[pp][0];
+            sh.sc[ld][2 * l + 1] = scw[pp][1];
+        }
     }
     __syncthreads();
     // running sums of every line, in the order of step 1
-    for (uint32_t i = tid; i < D; i += kSlabBlock) {
+    for (uint32_t i = tid; i < D; i += kSrowsBlock) {
         double a = 0.0;
         for (int c = 0; c < 14; ++c) {
             const uint32_t v0 = sh.sc[i][2 * c], v1 = sh.sc[i][2 * c + 1];
@@ -820,24 +842,26 @@ __global__ void __launch_bounds__(kSlabBlock) k_srows_select(Geom g, uint64_t n)
         }
     }
     __syncthreads();
-    // lane pp of each row draws for the row's line of pass pp
-    U4 dw;
-    {
-        const uint32_t kd = rg.kbase + (uint32_t)((l < P ? l : 0) * rows + row);
-        dw = philox10((uint32_t)n, (uint32_t)(n >> 32), rg.dom(kd), (uint32_t)rg.oct(kd, s), g.seed);
-    }
 #pragma unroll
     for (int pp = 0; pp < P; ++pp) {
         const uint32_t ld = (uint32_t)(pp * rows + row);
         const uint32_t ux = bcast_lane(dw.x, pp), uy = bcast_lane(dw.y, pp), uz = bcast_lane(dw.z, pp);
         const int cs = row_class(sh.acc[ld], ld < rg.nvalid, unit53(ux, uy) * Rmax, l, row);
+        // the row's octant and halo into LDS (its own lanes read them back)
+        uint32_t *oc = sh.oct[ld];
+#pragma unroll
+        for (int w = 0; w < 8; ++w) oc[8 * l + w] = raw[pp].W[w];
+        if (l < 12) *reinterpret_cast<uint4 *>(oc + kFxm + 4 * l) = uint4{raw[pp].F[0], raw[pp].F[1], raw[pp].F[2], raw[pp].F[3]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         slab_select(sh.sc[ld], sh.oct[ld], cs, uz, l, &sh.selq[ld], g.st);
     }
     __syncthreads();
     long long F = 0, dM = 0, dB = 0;
-    {
-        const uint32_t ld = (uint32_t)tid >> 2;
-        const int part = tid & 3;
+    for (uint32_t i = (uint32_t)tid; i < 4 * D; i += kSrowsBlock) {
+        const uint32_t ld = i >> 2;
+        const int part = (int)(i & 3u);
         const uint32_t f = ld < rg.nvalid ? sh.selq[ld] : kNoEvent;
         if (f != kNoEvent)
             slab_flip_part(g, sh.oct[ld], sh.sc[ld], sh.dco[ld], sh.nbdom[ld], rg.dom(rg.kbase + ld), rg.oct(rg.kbase + ld, s), f,
@@ -867,14 +891,12 @@ __global__ void __launch_bounds__(kSlabBlock) k_srows_select(Geom g, uint64_t n)
     __syncthreads();
     if (tid == 0) {
         F = dM = dB = 0;
-        for (int w = 0; w < kSlabBlock / 64; ++w) {
+        for (int w = 0; w < kSrowsBlock / 64; ++w) {
             F += sh.red[0][w];
             dM += sh.red[1][w];
             dB += sh.red[2][w];
         }
-        if (F) atomicAdd((unsigned long long *)&g.st->acc_fired[0], (unsigned long long)F);
-        if (dM) atomicAdd((unsigned long long *)&g.st->acc_dM[0], (unsigned long long)dM);
-        if (dB) atomicAdd((unsigned long long *)&g.st->acc_dB[0], (unsigned long long)dB);
+        add_counters(g, F, dM, dB);
     }
 }
 
@@ -898,13 +920,13 @@ hipError_t launch_slab_bin(const Geom &g, hipStream_t stream) {
 hipError_t launch_cycle_slab(const Geom &g, uint64_t n, hipStream_t stream) {
     if (!slab_rows_supported(g)) return hipErrorInvalidValue;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
-    const uint32_t grid = (uint32_t)((lines + kSlabDomains - 1) / kSlabDomains);
+    const uint32_t grid = (uint32_t)((lines + kSrowsLines - 1) / kSrowsLines);
     if (!(g.variant & SPKMC_VARIANT_RMAX_BOUND)) {
         const uint64_t units = (g.variant & SPKMC_VARIANT_RMAX_ALL) ? (uint64_t)g.K * 8u : lines;
         const uint32_t mgrid = (uint32_t)((units + 255) / 256);
         hipLaunchKernelGGL(k_srows_max<1>, dim3(mgrid), dim3(256), 0, stream, g, n);
     }
-    hipLaunchKernelGGL(k_srows_select<1>, dim3(grid), dim3(kSlabBlock), 0, stream, g, n);
+    hipLaunchKernelGGL(k_srows_select<1>, dim3(grid), dim3(kSrowsBlock), 0, stream, g, n);
     return hipGetLastError();
 }
 

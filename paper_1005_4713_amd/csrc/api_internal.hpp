@@ -71,6 +71,8 @@ struct spkmc_ctx {
     // primed_span (cycles run since their last set-up) is at least 2
     int primed_grid;
     uint64_t primed_cycle, primed_span;
+    // the slab counts in the state belong to the spins (per-cycle slab kernels)
+    bool counts_current;
     int engine;
     spkmc::ResidentShape res;      // CYCLE engine: the on-chip launch, where the lattice fits
     int grid, block, wg_domains;

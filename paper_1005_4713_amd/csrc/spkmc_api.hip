@@ -401,15 +401,20 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
         c->primed_cycle = c->cycle;
     } else {
         c->primed_grid = 0;
-        // PACKED lattices with octant edge 16 run the slab kernels, whose counts
-        // are binned afresh at the start of every run
-        const bool slab = slab_rows_supported(c->g);
-        if (slab && (e = launch_slab_bin(c->g, c->stream)) != hipSuccess) return hip_fail(c, e, "slab count kernel");
+        // PACKED lattices with octant edge 16 run the slab kernels, whose counts in the
+        // state follow every flip: binned only when something else changed the spins
+        // (a captured run bins for itself, and leaves nothing to the runs outside it)
+        const bool slab = slab_rows_supported(c->g), captured = slab && capturing(c->stream);
+        const bool current = c->counts_current && !captured;
+        c->counts_current = false;
+        if (slab && !current && (e = launch_slab_bin(c->g, c->stream)) != hipSuccess)
+            return hip_fail(c, e, "slab count kernel");
         for (uint64_t i = 0; i < ncycles; ++i) {
             e = launch_cycle(c->g, c->cycle, obs_every, c->stream, slab);
             if (e != hipSuccess) return hip_fail(c, e, "cycle kernel launch");
             c->cycle += 1;
         }
+        c->counts_current = slab && !captured;
     }
     return SPKMC_OK;
 }
@@ -485,7 +490,7 @@ spkmc_status spkmc_copy_spins(spkmc_ctx *c, int8_t *host, size_t n) {
 }
 
 spkmc_status spkmc_set_spins(spkmc_ctx *c, const int8_t *host, size_t n) {
-    if (c) c->primed_grid = 0;
+    if (c) c->primed_grid = 0, c->counts_current = false;
     if (!c) return fail(nullptr, SPKMC_E_INVAL, "ctx is NULL");
     if (!host) return fail(c, SPKMC_E_INVAL, "host is NULL");
     if (c->failed) return fail(c, SPKMC_E_STATE, "context is in a failed state");
@@ -536,7 +541,7 @@ spkmc_status spkmc_save(spkmc_ctx *c, void *host, size_t cap, size_t *n) {
 }
 
 spkmc_status spkmc_load(spkmc_ctx *c, const void *host, size_t n) {
-    if (c) c->primed_grid = 0;
+    if (c) c->primed_grid = 0, c->counts_current = false;
     if (!c) return fail(nullptr, SPKMC_E_INVAL, "ctx is NULL");
     if (!host) return fail(c, SPKMC_E_INVAL, "host is NULL");
     if (c->failed) return fail(c, SPKMC_E_STATE, "context is in a failed state");
@@ -688,6 +693,7 @@ static spkmc_status launch_planned(BatchPlan &bp, Replica *dev_reps, spkmc_batch
     for (size_t i = 0; i < bp.live.size(); ++i) {
         bp.live[i]->cycle += bp.nc[i];
         bp.live[i]->primed_grid = 0;  // a batch lays out the sync words for its own grid
+        bp.live[i]->counts_current = false;
     }
     batch_info_of(bp, info);
     return SPKMC_OK;
@@ -738,6 +744,7 @@ spkmc_status spkmc_batch_graph_create(spkmc_ctx *const *ctxs, size_t n, const ui
     for (spkmc_ctx *c : bp.live) {
         gr->expect.push_back(c->cycle);
         c->primed_grid = 0;
+        c->counts_current = false;
     }
     e = capture_batch(dev_reps, nl, bp.h, bp.P, bp.grid, bp.block, bp.lpd, &gr->graph);
     if (e == hipSuccess) e = hipGraphInstantiate(&gr->exec, gr->graph, nullptr, nullptr, 0);
@@ -767,6 +774,7 @@ spkmc_status spkmc_batch_graph_launch(spkmc_batch_graph *gr, uint32_t replays) {
         }
         for (size_t i = 0; i < gr->members.size(); ++i) {
             gr->members[i]->cycle += gr->nc[i];
+            gr->members[i]->counts_current = false;
             gr->expect[i] += gr->nc[i];
         }
     }

@@ -89,8 +89,8 @@ enum { SPKMC_LAYOUT_INT8 = 0, SPKMC_LAYOUT_PACKED = 1 };
  * exchange every cycle (PACKED layout, h = 8 or 16); every cycle bins the
  * active octant of every domain afresh.  With h = 16 and more lines than one
  * round of passes holds (up to 131 072 lines, e.g. two colours at L = 1024), the
- * wide mode keeps only each line's moments from the bin and derives the class
- * planes again for the selection, once the true R_max is known.
+ * wide mode bins and selects round by round on the predicted R_max and selects
+ * the few lines whose class the true R_max changes again.
  * INCREMENTAL: the persistent launch, but the class histograms of all octants
  * stay on chip and follow every flip (the flipped site and its six neighbours
  * change class); a cycle classifies its active octant only to locate the

@@ -61,15 +61,19 @@ namespace spkmc {
 // four words of padding: the histogram thread of line i reads line i's words as
 // 16-byte loads, and a stride of 32 words would put the lanes of a wavefront on
 // two bank offsets only).
-template <uint32_t DMAX, bool HISTP, int MW>
+template <uint32_t DMAX, bool HISTP, int MW, uint32_t MLINES = DMAX>
 struct PersistSharedT {
     double r[14];               // rate table
-    alignas(16) uint32_t mom[DMAX][MW];  // per line: the popcount moments of its active octant
+    alignas(16) uint32_t mom[MLINES][MW];  // per line: the popcount moments of its active octant
     uint32_t hist[DMAX][14];    // per line: class histogram (re-binning engine)
     uint32_t histp[HISTP ? DMAX : 1][8][7];  // per domain and octant: packed class counts (incremental engine)
     double acc[DMAX][14];       // per line: running FP64 sums of the frequency line
     double rk[DMAX];
     double uline[DMAX];         // per line: its event uniform of this cycle (speculative selection -> verification)
+    // wide mode: per line its site uniform, and the lines whose class the true R_max changed
+    uint32_t usite[MLINES < DMAX ? DMAX : 1];
+    uint32_t nredo;
+    uint16_t redo[MLINES < DMAX ? DMAX : 1];
     alignas(16) uint32_t zbuf[64][kRowHalo];  // per row: the six halo faces (8 words each), zeros (8)
     uint32_t nbdom[DMAX][6];    // per line: its domain's neighbour domains -x, +x, -y, +y, -z, +z
     uint32_t selq[DMAX];        // per line: (class << 12) | site q of its event, or kNoEvent
@@ -93,9 +97,9 @@ struct PersistSharedT {
 using PersistShared = PersistSharedT<kMaxWgDomains, false, 36>;
 using PersistSharedInc = PersistSharedT<kMaxWgDomains, true, 13>;
 // The wide mode (octant edge 16): RND = 2 or 4 rounds of four passes of 32 rows,
-// 256 or 512 lines per workgroup.
+// 256 or 512 lines per workgroup (the moments of one round at a time).
 template <int RND>
-using PersistSharedWide = PersistSharedT<32 * 4 * RND, false, 13>;
+using PersistSharedWide = PersistSharedT<32 * 4 * RND, false, 36, 32 * 4>;
 static_assert(sizeof(PersistSharedWide<4>) <= 160 * 1024, "wide-mode LDS exceeds a CU's 160 KB");
 
 // Bin octant o of every domain of the workgroup (the 13 moments of each row, then
@@ -144,8 +148,13 @@ __device__ __forceinline__ uint32_t row_lane(uint32_t v, int j) {
 }
 
 // RND > 1 (the wide mode, re-binning engine only): each row runs RND rounds of P
-// lines; the bin keeps only their moments, the selection waits for the true
-// R_max and derives every round's class planes again from the spins.
+// lines, each binned and selected on the predicted R_max before the next round
+// takes its registers.  Once the true R_max is known the few lines whose class
+// it changes (0.3 %) are gathered, and a row each loads, classifies and selects
+// them again.  Deriving every line's planes a second time for a selection with
+// the true R_max took 59 us per cycle for two colours at 1024^3, this 49.  (Rounds
+// of two passes with the next round's words in flight: 56; four passes with the
+// next round's first in flight: 49, and the register file spills.)
 // BND: 1 when the lattice may run with the fixed bound (read from the variant at
 // run time), 0 when it does not (the bound's code is compiled out: present in the
 // loop without running, it still slowed the cycle by about 2 %).
@@ -189,6 +198,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
     if (tid == 0) {
         sh.abort = 0;
         sh.pend_head = sh.pend_tail = 0;
+        sh.nredo = 0;
     }
     load_predictions(sh, xs);
     if (tid < 14) sh.r[tid] = g.r[tid];
@@ -311,8 +321,10 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
             }
             __syncthreads();
         } else if constexpr (RND > 1) {
-            // --- steps 1 and 4a, wide mode: the moments of every round's lines (the
-            // class planes are derived again for the selection)
+            // --- steps 1, 3, 4 and 4a, wide mode: round by round the class planes and
+            // moments, the frequency lines, and the selection on the predicted R_max
+            const double Rspec = bound ? rbound : sh.rpred[s];
+            constexpr uint32_t DR = (uint32_t)(rows * P);  // lines of a round
 #pragma unroll 1
             for (int r = 0; r < RND; ++r) {
                 Raw<H> raw[P];
@@ -326,40 +338,65 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
 #pragma unroll
                 for (int pp = 0; pp < P; ++pp) {
                     const uint32_t ld = (uint32_t)((r * P + pp) * rows + row);
-                    Planes<H> pw;
                     uint32_t m[13];
 #pragma unroll
                     for (int i = 0; i < 13; ++i) m[i] = 0;
-                    compute_octant<H, true>(raw[pp], ld < nvalid, l, sh.zbuf[row], pw, m);
-                    uint32_t mp[7];
+                    compute_octant<H, true>(raw[pp], ld < nvalid, l, sh.zbuf[row], pl[pp], m);
+                    uint32_t mp[7];  // sums over groups of four lanes, as in the one-round kernels
 #pragma unroll
-                    for (int i = 0; i < 6; ++i) mp[i] = row_scan(m[2 * i] | (m[2 * i + 1] << 16));
-                    mp[6] = row_scan(m[12]);
-                    if (l == 15) {
-#pragma unroll
-                        for (int i = 0; i < 6; ++i) {
-                            sh.mom[ld][2 * i] = mp[i] & 0xFFFFu;
-                            sh.mom[ld][2 * i + 1] = mp[i] >> 16;
-                        }
-                        sh.mom[ld][12] = mp[6];
+                    for (int i = 0; i < 6; ++i) mp[i] = quad_sum(m[2 * i] | (m[2 * i + 1] << 16));
+                    mp[6] = quad_sum(m[12]);
+                    if ((l & 3) == 3) {
+                        uint32_t *dst = &sh.mom[pp * rows + row][8 * (l >> 2)];
+                        *reinterpret_cast<uint4 *>(dst) = uint4{mp[0], mp[1], mp[2], mp[3]};
+                        *reinterpret_cast<uint4 *>(dst + 4) = uint4{mp[4], mp[5], mp[6], 0u};
                     }
                 }
-            }
-            __syncthreads();
-            for (uint32_t i = tid; i < D; i += nthr) {
-                uint32_t mm[13], hc[14];
-                for (int c = 0; c < 13; ++c) mm[c] = sh.mom[i][c];
-                hist_from_moments(mm, g.h3, hc);
-                double a = 0.0;
-                for (int c = 0; c < 14; ++c) {
-                    double term = (double)hc[c] * sh.r[c];
-                    a = a + term;
-                    sh.acc[i][c] = a;
-                    sh.hist[i][c] = hc[c];
+                __syncthreads();
+                if (!drawn && (uint32_t)(tid & ~63) >= DR) {  // no line of this wavefront to histogram
+                    draw();
+                    drawn = true;
                 }
-                sh.rk[i] = i < nvalid ? a : 0.0;
+                for (uint32_t i = tid; i < DR; i += nthr) {
+                    const uint32_t ld = (uint32_t)r * DR + i;
+                    uint32_t mm[13], hc[14], w[7] = {0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int c = 0; c < 7; ++c) w[c] += sh.mom[i][8 * q + c];
+#pragma unroll
+                    for (int c = 0; c < 6; ++c) {
+                        mm[2 * c] = w[c] & 0xFFFFu;
+                        mm[2 * c + 1] = w[c] >> 16;
+                    }
+                    mm[12] = w[6];
+                    hist_from_moments(mm, g.h3, hc);
+                    double a = 0.0;
+                    for (int c = 0; c < 14; ++c) {
+                        double term = (double)hc[c] * sh.r[c];
+                        a = a + term;
+                        sh.acc[ld][c] = a;
+                        sh.hist[ld][c] = hc[c];
+                    }
+                    sh.rk[ld] = ld < nvalid ? a : 0.0;
+                }
+                __syncthreads();
+                if (!drawn) draw();
+                drawn = true;
+#pragma unroll
+                for (int pp = 0; pp < P; ++pp) {
+                    const int j = r * P + pp;
+                    const uint32_t ld = (uint32_t)(j * rows + row);
+                    const uint32_t ux = row_lane(dw.x, j), uy = row_lane(dw.y, j), uz = row_lane(dw.z, j);
+                    const double u = unit53(ux, uy);
+                    if (l == 0) {
+                        sh.uline[ld] = u;
+                        sh.usite[ld] = uz;
+                    }
+                    const int cs = row_class(sh.acc[ld], ld < nvalid, u * Rspec, l, row);
+                    select_site<H>(pl[pp], cs, cs >= 0 ? sh.hist[ld][cs] : 0u, uz, l, &sh.selq[ld], st);
+                }
             }
-            __syncthreads();
         } else {
             // --- steps 1 and 4a: class planes and moments of the active octants
             // (the words of every pass in flight at once; each pass's raw words
@@ -533,29 +570,29 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         s_next = sh.next_colour;
 
         if constexpr (RND > 1) {
-            // --- steps 3, 4 and 4b, wide mode: every round's class planes from its
-            // words, then the selection with the true R_max
-#pragma unroll 1
-            for (int r = 0; r < RND; ++r) {
-                Raw<H> raw[P];
-#pragma unroll
-                for (int pp = 0; pp < P; ++pp) {
-                    const uint32_t ld = (uint32_t)((r * P + pp) * rows + row);
-                    const bool valid = ld < nvalid;
-                    load_octant<H>(g, line_dom(kbase + ld), line_oct(kbase + ld, s), valid, l,
-                                   sh.nbdom[valid ? ld : 0], raw[pp]);
-                }
-#pragma unroll
-                for (int pp = 0; pp < P; ++pp) {
-                    const int j = r * P + pp;
+            // wide mode: the lines whose class differs under the true R_max, a row each
+            // (the selected class is in the line's slot)
+            if (!bound) {
+                if (tid == 0) sh.rpred[s] = Rmax;
+#pragma unroll 4
+                for (int j = 0; j < P * RND; ++j) {
                     const uint32_t ld = (uint32_t)(j * rows + row);
-                    const bool valid = ld < nvalid;
-                    Planes<H> pw;
+                    const int cs = row_class(sh.acc[ld], ld < nvalid, sh.uline[ld] * Rmax, l, row);
+                    const uint32_t f = sh.selq[ld];
+                    if (l == 0 && cs != (f == kNoEvent ? -1 : (int)(f >> 12)))
+                        sh.redo[atomicAdd(&sh.nredo, 1u)] = (uint16_t)ld;
+                }
+                __syncthreads();
+                const uint32_t nredo = sh.nredo;
+#pragma unroll 1
+                for (uint32_t i = (uint32_t)row; i < nredo; i += (uint32_t)rows) {
+                    const uint32_t ld = sh.redo[i];
+                    Raw<H> raw;
+                    load_octant<H>(g, line_dom(kbase + ld), line_oct(kbase + ld, s), true, l, sh.nbdom[ld], raw);
                     uint32_t m[13];
-                    compute_octant<H, false>(raw[pp], valid, l, sh.zbuf[row], pw, m);
-                    const uint32_t ux = row_lane(dw.x, j), uy = row_lane(dw.y, j), uz = row_lane(dw.z, j);
-                    const int cs = row_class(sh.acc[ld], valid, unit53(ux, uy) * Rmax, l, row);
-                    select_site<H>(pw, cs, cs >= 0 ? sh.hist[ld][cs] : 0u, uz, l, &sh.selq[ld], st);
+                    compute_octant<H, false>(raw, true, l, sh.zbuf[row], pl[0], m);
+                    const int cs = row_class(sh.acc[ld], true, sh.uline[ld] * Rmax, l, row);
+                    select_site<H>(pl[0], cs, cs >= 0 ? sh.hist[ld][cs] : 0u, sh.usite[ld], l, &sh.selq[ld], st);
                 }
             }
         } else if (!bound) {
@@ -576,6 +613,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         // such row, one per axis, each moving the
         // classes of the flipped site's two neighbours along its axis; the first
         // also flips the site (spin word and halo copies) and moves its class
+        if (RND > 1 && tid == 0) sh.nredo = 0;  // read before the barrier, next used after the coming one
         const uint32_t nwork = INC ? 3 * D : D;
         for (uint32_t t = tid; t < nwork; t += nthr) {
             const uint32_t ld = INC ? t / 3 : t, ax = INC ? t % 3 : 0;

@@ -27,9 +27,9 @@
 // Between workgroups: the R_max slots of the persistent kernels (bank n & 1,
 // generation bit 63), and one 64-bit event record per frequency line (cycle in
 // the upper half, bank n & 1).  A workgroup applies the events of the
-// neighbouring domains it does not own to its own sites: before the frequency
-// lines where the colour change makes them matter, else while the other maxima
-// travel.  The records carry their cycle, so no flip has to be waited for.
+// neighbouring domains it does not own to its own sites: at the end of the cycle
+// where the next colour makes them matter, else while the next maxima travel.
+// The records carry their cycle, so no flip has to be waited for.
 #include <string>
 
 #include "persistent_common.hpp"
@@ -44,7 +44,7 @@ constexpr uint32_t kPadByte = 15;  // bytes past an octant's last site: a value 
 struct ResidentHead {
     double r[16];                 // rate of each byte value
     unsigned long long wmax[16];  // per wavefront: its largest line
-    unsigned long long stat[2];   // this workgroup's counters of cycle n (bank n & 1)
+    unsigned long long stat[4];   // this workgroup's counters of cycle n (bank n & 3)
     double lnu[4];                // -ln u of the clock step of cycle n (place n & 3)
     double rmax;
     int colour[4];                // colour of cycle n (place n & 3)
@@ -56,11 +56,7 @@ static_assert(sizeof(ResidentHead) <= kHeadBytes, "head");
 // class c (7 [up] + aligned) <-> byte value 8 [up] + up neighbours
 __device__ __forceinline__ int byte_of_class(int c) { return c >= 7 ? c + 1 : 6 - c; }
 
-// Counters of one cycle, packed: fired, of these up spins, sum of aligned counts.
 constexpr unsigned long long kGenBit = 1ull << 63;
-__device__ __forceinline__ unsigned long long stat_of(int cs) {
-    return 1ull | ((unsigned long long)(cs >= 7) << 20) | ((unsigned long long)(cs % 7) << 40);
-}
 
 __device__ __forceinline__ uint32_t match_bits(uint32_t w, uint32_t pat) {  // bit 4 of every byte equal to the pattern's
     return (0x10101010u - (w ^ pat)) & 0x10101010u;
@@ -113,9 +109,10 @@ __device__ __forceinline__ uint32_t spin_near(const Geom &g, uint32_t k, const i
 
 }  // namespace
 
-// GS: lanes per frequency line.
-template <int GS>
-__global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
+// GS: lanes per frequency line; MAXT: threads at most (640: the usual 512 of lines and
+// two service wavefronts, whose registers do not spill; 1024 spills 46).
+template <int GS, int MAXT>
+__global__ void __launch_bounds__(MAXT) k_resident(ResidentArgs A) {
     extern __shared__ uint4 lds_raw[];
     const Geom &g = A.g;
     const uint32_t gid = blockIdx.x, G = A.G;
@@ -147,7 +144,7 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
     if (tid < 16) sh.wmax[tid] = 0;  // of wavefronts this launch has not
     if (tid == 0) {
         sh.abort = 0;
-        sh.stat[0] = sh.stat[1] = 0;
+        sh.stat[0] = sh.stat[1] = sh.stat[2] = sh.stat[3] = 0;
     }
     for (uint32_t i = (uint32_t)tid; i < nown * 6; i += nthr) {
         const int dir = (int)(i % 6), a = dir >> 1;
@@ -273,7 +270,7 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
     // the record keeper's totals since launch start (workgroup 0, service wavefront)
     long long totF = 0, totU = 0, totA = 0;
     const bool keeper = gid == 0 && svc;
-    double t = 0.0;
+    double t = 0.0, t_prev = 0.0;  // the clock now and a cycle ago
     uint64_t fired0 = 0, nulls0 = 0, recs = 0, next_rec = ~0ull;
     int64_t M0 = 0, B0 = 0;
     uint32_t ring = 0;  // the next record's place: recs mod rec_cap
@@ -287,29 +284,46 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         if (g.rec_cap) ring = (uint32_t)(recs % g.rec_cap);
         if (A.obs_every) next_rec = (n0 / A.obs_every + 1) * A.obs_every;
     }
-    // counters of cycle m into the totals (every workgroup has finished it, or is about
-    // to); a whole cycle's counters fit the packed fields (fewer than 2^20 lines)
+    // counters of cycle m (packed: fired, of these up spins << 20, sum of aligned counts
+    // << 40) into the totals; a whole cycle's fit the fields (fewer than 2^20 lines).
+    // Two cycles late, when every workgroup's have arrived: read in the next cycle they
+    // kept workgroup 0, and so all, waiting (0.9 us per cycle at L = 128).
     auto gather = [&](uint64_t m) {
         unsigned long long sum = 0;
         if (G == 1) {
-            sum = sh.stat[m & 1];
+            sum = sh.stat[m & 3];
+            if (lane == 0) sh.stat[m & 3] = 0;
         } else {
-            const unsigned long long gen = ((m >> 1) & 1) << 63;
-            for (uint32_t w = (uint32_t)lane; w < G; w += 64) {
-                const uint64_t *p = A.part + (m & 1) * (uint64_t)G + w;
-                unsigned long long v = ld64(p);
-                if ((v & kGenBit) != gen) {
-                    const uint64_t start = now_ticks();
-                    while (((v = ld64(p)) & kGenBit) != gen) {
-                        __builtin_amdgcn_s_sleep(1);
-                        if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
-                            atomicOr(&st->error, kErrFlagTimeout);
-                            sh.abort = 1;
-                            break;
+            const unsigned long long gen = ((m >> 2) & 1) << 63;
+            const uint64_t *bank = A.part + (m & 3) * (uint64_t)G;
+            const uint64_t start = now_ticks();
+            for (uint32_t base = 0; base < G; base += 256) {
+                unsigned long long v[4];  // in flight together
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = base + (uint32_t)(i * 64 + lane);
+                    v[i] = w < G ? ld64(&bank[w]) : gen;
+                }
+                for (;;) {
+                    bool all = true;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const uint32_t w = base + (uint32_t)(i * 64 + lane);
+                        if ((v[i] & kGenBit) != gen) {
+                            all = false;
+                            v[i] = ld64(&bank[w]);
                         }
                     }
+                    if (__all(all)) break;
+                    __builtin_amdgcn_s_sleep(1);
+                    if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
+                        atomicOr(&st->error, kErrFlagTimeout);
+                        sh.abort = 1;
+                        break;
+                    }
                 }
-                sum += v & ~kGenBit;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum += v[i] & ~kGenBit;
             }
             for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
         }
@@ -318,13 +332,13 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
         totA += (long long)((sum >> 40) & 0x7FFFFFu);
     };
     // the state after `cyc` cycles: the ring record, or at the end the counters
-    auto keep = [&](uint64_t cyc, bool record, bool final) {
+    auto keep = [&](uint64_t cyc, double at, bool record, bool final) {
         if (lane != 0) return;
         spkmc_record r;
         r.cycle = cyc;
         r.fired = fired0 + (uint64_t)totF;
         r.nulls = nulls0 + (uint64_t)NL * (cyc - n0) - (uint64_t)totF;
-        r.t = t;
+        r.t = at;
         r.M = M0 + 2 * totF - 4 * totU;   // an up spin takes 2 from M, a down spin adds 2
         r.B = B0 + 12 * totF - 4 * totA;  // six bonds, `aligned` of them with the old spin
         if (record) {
@@ -336,13 +350,22 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             st->cycle = cyc;
             st->fired = r.fired;
             st->nulls = r.nulls;
-            st->t = t;
+            st->t = at;
             st->M = r.M;
             st->B = r.B;
             st->rec_count = recs;
         }
     };
 
+    // the counters of cycle m gathered, and its record appended if one is due (the clock
+    // is a cycle ahead)
+    auto note = [&](uint64_t m) {
+        gather(m);
+        if (m + 1 == next_rec) {
+            if (g.rec_cap) keep(m + 1, t_prev, true, false);
+            next_rec += A.obs_every;
+        }
+    };
     auto draw = [&](uint64_t n, int colour, uint32_t f) {
         const uint32_t line = lbase + f;
         return philox10((uint32_t)n, (uint32_t)(n >> 32), lpd == 1 ? line : line >> 2, (uint32_t)line_oct(f, colour),
@@ -368,20 +391,9 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
     const bool one = nl <= groups;  // a single round of lines: sums and draws stay in registers
     __syncthreads();
     s = sh.colour[n0 & 3];
+    bool pending = false;  // events of the previous cycle (colour prev) still to apply
 
     for (uint64_t n = n0; n < n_end; ++n) {
-        // --- step 6: events of the previous cycle in other workgroups' domains, now where
-        // the frequency lines of this cycle can see them
-        bool pending = G > 1 && n > n0;
-        if (pending) {
-            const int diff = s ^ prev;
-            if (rmax_all || (lpd == 4 ? diff != 0 : diff && !(diff & (diff - 1)))) {
-                apply_events(n - 1, prev, (uint32_t)tid, (uint32_t)nthr);
-                pending = false;
-                __syncthreads();
-                if (sh.abort) break;
-            }
-        }
         // --- steps 1 and 2: the frequency lines and the workgroup's largest
         double acc[14], m = 0.0;
         for (uint32_t f = group; f < nl; f += groups) {
@@ -450,14 +462,7 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
                 sh.lnu[(n + 2) & 3] = -log(cd.ut);
             }
         } else if (svc) {
-            if (gid == 0 && n > n0) {
-                gather(n - 1);
-                if (n == next_rec) {
-                    if (g.rec_cap) keep(n, true, false);
-                    next_rec += A.obs_every;
-                }
-                if (G == 1 && lane == 0) sh.stat[(n - 1) & 1] = 0;
-            }
+            if (gid == 0 && n > n0 + 1) note(n - 2);
         } else if (wave != 0) {
             if (pending) apply_events(n - 1, prev, (uint32_t)tid - 64, (uint32_t)nthr - 192);
         }
@@ -535,17 +540,28 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
                 st64(A.rec + (n & 1) * (uint64_t)NL + lbase + f,
                      ((uint64_t)(uint32_t)(n + 1) << 32) |
                          (event ? 0x80000000u | ((uint32_t)(cs >= 7) << 30) | q : 0u));
+            {   // the counters of this wavefront's lines (one lane of each speaks)
+                const bool speak = event && l == 0;
+                const uint64_t ev = __ballot(speak), ups = __ballot(speak && cs >= 7);
+                const uint32_t al = (uint32_t)(cs >= 7 ? cs - 7 : cs);
+                unsigned long long sum = (unsigned long long)__popcll(ev) | ((unsigned long long)__popcll(ups) << 20);
+#pragma unroll
+                for (int b = 0; b < 3; ++b)
+                    sum += (unsigned long long)__popcll(__ballot(speak && ((al >> b) & 1u))) << (40 + b);
+                if (lane == 0 && sum) atomicAdd(&sh.stat[n & 3], sum);
+            }
             if (!event) continue;
             const int up = cs >= 7, dn = up ? -1 : 1;
             const Site sc = site_of(q, A);
-            if (l < 6) {
-                // the neighbour in direction l, where this workgroup owns it
+            if (l < 7) {
+                // the neighbour in direction l, where this workgroup owns it; lane 6: the
+                // site itself, whose byte changes by 8
                 const int a = l >> 1, side = l & 1;
                 Site t = sc;
                 uint32_t toct = oct;
-                const int x = (a == 0 ? sc.c[0] : a == 1 ? sc.c[1] : sc.c[2]) + (side ? 1 : -1);
+                const int x = l == 6 ? 0 : (a == 0 ? sc.c[0] : a == 1 ? sc.c[1] : sc.c[2]) + (side ? 1 : -1);
                 int to = x;
-                if (x < 0 || x == h) {
+                if (l != 6 && (x < 0 || x == h)) {
                     to = side ? 0 : h - 1;
                     uint32_t tl = ld;
                     if (((o >> a) & 1) == side) tl = nbr[ld * 6 + l] - kbase;
@@ -553,15 +569,9 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
                 }
                 if (a == 0) t.c[0] = to;
                 else if (a == 1) t.c[1] = to;
-                else t.c[2] = to;
-                if (toct != ~0u) bump(toct, index_of(t, h), dn);
-            } else if (l == 6) {
-                atomicXor(&cls[oct * ow + (q >> 2)], 8u << (8 * (q & 3)));
-                const uint32_t now = v ^ 8u;
-                atomicAdd(&cnt[oct * 8 + (v >> 1)], 0u - (1u << (16 * (v & 1))));
-                atomicAdd(&cnt[oct * 8 + (now >> 1)], 1u << (16 * (now & 1)));
+                else if (a == 2) t.c[2] = to;
+                if (toct != ~0u) bump(toct, index_of(t, h), l == 6 ? 8 * dn : dn);
             } else if (l == 8) {
-                atomicAdd(&sh.stat[n & 1], stat_of(cs));
                 if (g.layout == SPKMC_LAYOUT_INT8) {
                     const uint32_t X = (uint32_t)((o & 1) * h + sc.c[0]), Y = (uint32_t)(((o >> 1) & 1) * h + sc.c[1]);
                     const uint32_t Z = (uint32_t)(((o >> 2) & 1) * h + sc.c[2]);
@@ -582,19 +592,35 @@ __global__ void __launch_bounds__(1024) k_resident(ResidentArgs A) {
             }
         }
         // --- step 5, in the record keeper's wavefront (the others need no clock)
-        if (svc) t = t + sh.lnu[n & 3] / (clock_s * Rmax);
+        if (svc) {
+            t_prev = t;
+            t = t + sh.lnu[n & 3] / (clock_s * Rmax);
+        }
+        // --- step 6: this cycle's events in other workgroups' domains, now where the next
+        // cycle's frequency lines can see them (by the wavefronts with no or few lines,
+        // while the others flip), else while the next maxima travel
+        const int next = sh.colour[(n + 1) & 3], diff = s ^ next;
+        pending = G > 1;
+        if (G > 1 && n + 1 < n_end && (rmax_all || (lpd == 4 ? diff != 0 : diff && !(diff & (diff - 1))))) {
+            pending = false;
+            if (wave >= nwaves - 2) apply_events(n, s, (uint32_t)(tid - 64 * (nwaves - 2)), 128u);
+        }
         prev = s;
+        s = next;
         __syncthreads();
-        s = sh.colour[(n + 1) & 3];
-        if (G > 1 && tid == 0) {
-            st64(A.part + (n & 1) * (uint64_t)G + gid, sh.stat[n & 1] | gen);
-            sh.stat[n & 1] = 0;
+        if (G > 1) {
+            if (sh.abort) break;
+            if (tid == 0) {
+                st64(A.part + (n & 3) * (uint64_t)G + gid, sh.stat[n & 3] | (((n >> 2) & 1) << 63));
+                sh.stat[n & 3] = 0;
+            }
         }
     }
     __syncthreads();
     if (keeper && !sh.abort) {
+        if (A.ncycles > 1) note(n_end - 2);
         gather(n_end - 1);
-        if (!sh.abort) keep(n_end, n_end == next_rec && g.rec_cap, true);
+        if (!sh.abort) keep(n_end, t, n_end == next_rec && g.rec_cap, true);
     }
 }
 
@@ -605,18 +631,19 @@ __global__ void k_resident_prep(ResidentArgs A) {
     const uint64_t NL = (uint64_t)A.g.K * A.g.lpd;
     if (i < 2 * NL) A.rec[i] = A.n0 << 32;
     if (i < A.G)
-        for (uint64_t nb = A.n0; nb < A.n0 + 2; ++nb) {
-            const uint64_t v = (((nb >> 1) + 1) & 1) << 63;
-            A.slot[(nb & 1) * A.G + i] = v;
-            A.part[(nb & 1) * A.G + i] = v;
+        for (uint64_t nb = A.n0; nb < A.n0 + 4; ++nb) {
+            if (nb < A.n0 + 2) A.slot[(nb & 1) * A.G + i] = (((nb >> 1) + 1) & 1) << 63;
+            A.part[(nb & 3) * A.G + i] = (((nb >> 2) + 1) & 1) << 63;
         }
 }
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-static void *resident_kernel(int gs) {
-    return gs == 16 ? reinterpret_cast<void *>(&k_resident<16>) : reinterpret_cast<void *>(&k_resident<64>);
+static void *resident_kernel(int gs, int block) {
+    if (block <= 640)
+        return gs == 16 ? reinterpret_cast<void *>(&k_resident<16, 640>) : reinterpret_cast<void *>(&k_resident<64, 640>);
+    return gs == 16 ? reinterpret_cast<void *>(&k_resident<16, 1024>) : reinterpret_cast<void *>(&k_resident<64, 1024>);
 }
 
 bool resident_configure(const Geom &g, ResidentShape &out) {
@@ -660,7 +687,7 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     out.block = (int)thr;
     out.lds = (size_t)(kHeadBytes + D * per_domain);
     if (G == 1) out.lds += (size_t)(32 * lines + 32);  // the lines' numbers, two cycles of them
-    void *kern = resident_kernel(gs);
+    void *kern = resident_kernel(gs, out.block);
     (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out.lds);
     int occ = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, out.block, out.lds) != hipSuccess || occ < 1) {
@@ -678,7 +705,7 @@ hipError_t launch_resident(const Geom &g, const ResidentShape &shape, uint64_t n
     A.g = g;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
     // the per-cycle engine's histograms (8 words per line), unused here: two banks of
-    // records, then the slots and the counters (4 words per workgroup, G <= lines)
+    // records, then the slots and the counters (6 words per workgroup, G <= lines)
     A.rec = reinterpret_cast<uint64_t *>(g.hist);
     A.slot = A.rec + 2 * lines;
     A.part = A.slot + 2 * (uint64_t)shape.G;
@@ -690,7 +717,7 @@ hipError_t launch_resident(const Geom &g, const ResidentShape &shape, uint64_t n
     A.ow = (g.h3 + 3) / 4;
     A.W = ((A.ow + (uint32_t)shape.gs - 1) / (uint32_t)shape.gs) | 1u;
     A.hinv = g.h == 1 ? 0u : (uint32_t)(((1ull << 32) + (uint64_t)g.h - 1) / (uint64_t)g.h);
-    void *kern = resident_kernel(shape.gs);
+    void *kern = resident_kernel(shape.gs, shape.block);
     void *args[] = {&A};
     if (shape.G == 1)
         return hipLaunchKernel(kern, dim3(1), dim3(shape.block), args, shape.lds, stream);

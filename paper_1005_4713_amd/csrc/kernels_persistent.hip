@@ -182,6 +182,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
     auto line_oct = [=](uint32_t line, int colour) {
         return lpd == 1 ? colour : two_colour_octant(colour, line & 3u);
     };
+    const uint32_t ss = slot_shift(g);
     const bool recorder = gid == 0;
     const uint64_t n_end = n0 + ncycles;
 
@@ -253,17 +254,17 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         // octant's counts are needed) the wait covers every neighbour every cycle.
         if (n > n0) {
             if (bound || rmax_all) {
-                if (!wait_neighbours<BLOCK>(xs, st, sh, G, -1, n)) break;
+                if (!wait_neighbours<BLOCK>(xs, st, sh, G, -1, n, ss)) break;
             } else if (lpd == 4) {
                 // two colours: after a colour change every face of an active octant
                 // touches the cells flipped in the previous cycle
-                if (s != prev_colour && !wait_neighbours<BLOCK>(xs, st, sh, G, -1, n)) break;
+                if (s != prev_colour && !wait_neighbours<BLOCK>(xs, st, sh, G, -1, n, ss)) break;
             } else {
                 int diff = s ^ prev_colour;
                 if (diff && !(diff & (diff - 1))) {
                     int a = diff == 1 ? 0 : diff == 2 ? 1 : 2;
                     int dir = 2 * a + ((s >> a) & 1);  // below (-) if bit a of s is 0, else above (+)
-                    if (!wait_neighbours<BLOCK>(xs, st, sh, G, dir, n)) break;
+                    if (!wait_neighbours<BLOCK>(xs, st, sh, G, dir, n, ss)) break;
                 }
             }
         }
@@ -465,13 +466,13 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
 
         // --- step 2: R_max over all active octants
         // bank n & 1 holds cycles n - 2 and n; the generation bit tells them apart
-        uint64_t *bank = xs.slot + (n & 1) * (uint64_t)G;
+        uint64_t *bank = xs.slot + (((n & 1) * (uint64_t)G) << ss);
         const uint64_t gen = ((n >> 1) & 1) << 63;
         if (tid < 64 && !bound) {
             double v = 0.0;
             for (uint32_t i = tid; i < D; i += 64) v = fmax(v, sh.rk[i]);
             v = wave_max_nonneg(v);
-            if (tid == 63) st64(&bank[gid], double_to_bits(v) | gen);
+            if (tid == 63) st64(&bank[gid << ss], double_to_bits(v) | gen);
         }
         if constexpr (INC) {
             // the active octants' class planes, while the other maxima travel
@@ -538,7 +539,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
 #pragma unroll
                 for (int i = 0; i < kSlotsPerLane; ++i) {
                     uint32_t w = base + (uint32_t)i * 64 + tid;
-                    sv[i] = w < G ? ld64(&bank[w]) : gen;
+                    sv[i] = w < G ? ld64(&bank[w << ss]) : gen;
                 }
                 for (;;) {
                     bool all = true;
@@ -547,7 +548,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                         uint32_t w = base + (uint32_t)i * 64 + tid;
                         if ((sv[i] & (1ull << 63)) != gen) {
                             all = false;
-                            sv[i] = ld64(&bank[w]);
+                            sv[i] = ld64(&bank[w << ss]);
                         }
                     }
                     if (__all(all)) break;
@@ -759,14 +760,14 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
             // (each thread waited for its own before the barrier)
             if (!indep) {
                 if (record || last) __builtin_amdgcn_s_waitcnt(0);
-                st64(&xs.flag[gid], n + 1);
+                st64(&xs.flag[gid << ss], n + 1);
             }
         }
         if (bound && record && !last) {  // uniform over the workgroup
             if (recorder && tid < 64) {
                 // fixed bound: workgroup 0 appends the record as soon as every
                 // workgroup has completed the cycle (its own flag is already out)
-                if (wait_all_flags(xs, st, sh, G, tid, n + 1)) {
+                if (wait_all_flags(xs, st, sh, G, tid, n + 1, ss)) {
                     emit_record(g, xs, sh, G, tid, n0, fired0, nulls0, M0, B0);
                     if (tid == 0) st64(xs.emitted, (uint64_t)rec_index);
                 }
@@ -779,7 +780,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
     // end of the launch: workgroup 0 waits for every workgroup to finish, then
     // appends the records still pending and the record of the last cycle
     if (recorder) {
-        if (tid < 64 && !sh.abort) wait_all_flags(xs, st, sh, G, tid, n_end);
+        if (tid < 64 && !sh.abort) wait_all_flags(xs, st, sh, G, tid, n_end, ss);
         __syncthreads();
         if (tid < 64 && !sh.abort) {
             while (sh.pend_head != sh.pend_tail) {
@@ -846,22 +847,22 @@ __global__ void __launch_bounds__(BLOCK) k_persistent_batch(const Replica *__res
 // flags the start cycle.  (The end of a launch of at least two cycles leaves
 // both in exactly this state for a launch of the same shape that continues
 // where it stopped.)
-__device__ __forceinline__ void prep_one(const PersistScratch &xs, uint32_t G, uint64_t n0, uint32_t i) {
+__device__ __forceinline__ void prep_one(const PersistScratch &xs, uint32_t ss, uint32_t G, uint64_t n0, uint32_t i) {
     // bank b first serves cycle nb (n0 or n0 + 1, nb & 1 == b): mark it "not yet"
-    for (uint64_t nb = n0; nb < n0 + 2; ++nb) xs.slot[(nb & 1) * G + i] = (((nb >> 1) + 1) & 1) << 63;
-    xs.flag[i] = n0;
+    for (uint64_t nb = n0; nb < n0 + 2; ++nb) xs.slot[((nb & 1) * G + i) << ss] = (((nb >> 1) + 1) & 1) << 63;
+    xs.flag[(uint64_t)i << ss] = n0;
     if (i == 0) *xs.emitted = 0;
 }
 // and (incremental engine) no pushed class changes pending: the launch starts
 // from histograms binned afresh.
-__global__ void k_persistent_prep(PersistScratch xs, uint32_t G, uint64_t n0, uint64_t *dh, uint64_t ndh) {
+__global__ void k_persistent_prep(PersistScratch xs, uint32_t ss, uint32_t G, uint64_t n0, uint64_t *dh, uint64_t ndh) {
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < G) prep_one(xs, G, n0, (uint32_t)i);
+    if (i < G) prep_one(xs, ss, G, n0, (uint32_t)i);
     for (uint64_t w = i; w < ndh; w += (uint64_t)gridDim.x * blockDim.x) dh[w] = 0;
 }
 __global__ void k_persistent_prep_batch(const Replica *__restrict__ reps, uint32_t nrep, int zero_dh) {
     for (uint32_t r = blockIdx.x; r < nrep; r += gridDim.x) {
-        for (uint32_t i = threadIdx.x; i < reps[r].G; i += blockDim.x) prep_one(reps[r].xs, reps[r].G, reps[r].n0, i);
+        for (uint32_t i = threadIdx.x; i < reps[r].G; i += blockDim.x) prep_one(reps[r].xs, slot_shift(reps[r].g), reps[r].G, reps[r].n0, i);
         if (zero_dh) {
             const uint64_t ndh = (uint64_t)reps[r].g.K * 16;
             for (uint64_t w = threadIdx.x; w < ndh; w += blockDim.x) reps[r].g.dh[w] = 0;
@@ -1001,8 +1002,8 @@ uint64_t persistent_scratch_words(uint64_t K) { return kScratchWordsPerWg * (K /
 
 PersistScratch scratch_of(const Geom &g, int G) {
     PersistScratch xs;
-    xs.slot = g.sync;
-    xs.flag = g.sync + 2 * (uint64_t)G;
+    xs.slot = reinterpret_cast<uint64_t *>(g.hist);
+    xs.flag = xs.slot + ((2 * (uint64_t)G) << slot_shift(g));
     xs.recp = reinterpret_cast<int64_t *>(g.sync + 3 * (uint64_t)G);
     xs.fin = reinterpret_cast<int64_t *>(g.sync + 15 * (uint64_t)G);
     xs.emitted = g.sync + 18 * (uint64_t)G;                  // within the 16 spare words
@@ -1030,8 +1031,8 @@ hipError_t launch_persistent(const Geom &g, uint64_t n0, uint64_t ncycles, uint3
         const uint64_t ndh = inc ? (uint64_t)g.K * 16 : 0;
         uint64_t blocks = ((uint64_t)grid + 255) / 256, bdh = (ndh + 255) / 256;
         blocks = blocks > bdh ? blocks : (bdh < 2048 ? bdh : 2048);
-        hipLaunchKernelGGL(k_persistent_prep, dim3((uint32_t)blocks), dim3(256), 0, stream, xs, (uint32_t)grid, n0,
-                           g.dh, ndh);
+        hipLaunchKernelGGL(k_persistent_prep, dim3((uint32_t)blocks), dim3(256), 0, stream, xs, slot_shift(g),
+                           (uint32_t)grid, n0, g.dh, ndh);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1048,8 +1049,8 @@ hipError_t launch_persistent(const Geom &g, uint64_t n0, uint64_t ncycles, uint3
     return launch_resident_grid(kern, grid, block, args, stream);
 }
 
-hipError_t launch_persistent_prep(const PersistScratch &xs, uint32_t G, uint64_t n0, hipStream_t stream) {
-    hipLaunchKernelGGL(k_persistent_prep, dim3((G + 255) / 256), dim3(256), 0, stream, xs, G, n0, (uint64_t *)nullptr,
+hipError_t launch_persistent_prep(const Geom &g, const PersistScratch &xs, uint32_t G, uint64_t n0, hipStream_t stream) {
+    hipLaunchKernelGGL(k_persistent_prep, dim3((G + 255) / 256), dim3(256), 0, stream, xs, slot_shift(g), G, n0, (uint64_t *)nullptr,
                        (uint64_t)0);
     return hipGetLastError();
 }

@@ -420,8 +420,8 @@ __global__ void __launch_bounds__(MAXT) k_resident(ResidentArgs A) {
             // the exchange also keeps the workgroups within a cycle of one another)
             double v = !bound && lane < nwaves ? bits_to_double(sh.wmax[lane < 16 ? lane : 15]) : 0.0;
             v = wave_max_nonneg(v);
-            uint64_t *bank = A.slot + (n & 1) * (uint64_t)G;
-            if (lane == 63) st64(&bank[gid], double_to_bits(v) | gen);
+            uint64_t *bank = A.slot + A.apart * ((n & 1) * (uint64_t)G);
+            if (lane == 63) st64(&bank[A.apart * gid], double_to_bits(v) | gen);
             double best = 0.0;
             const uint64_t start = now_ticks();
             for (uint32_t base = 0; base < G; base += 256) {
@@ -429,7 +429,7 @@ __global__ void __launch_bounds__(MAXT) k_resident(ResidentArgs A) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t w = base + (uint32_t)(i * 64 + lane);
-                    sv[i] = w < G ? ld64(&bank[w]) : gen;
+                    sv[i] = w < G ? ld64(&bank[A.apart * w]) : gen;
                 }
                 for (;;) {
                     bool all = true;
@@ -438,7 +438,7 @@ __global__ void __launch_bounds__(MAXT) k_resident(ResidentArgs A) {
                         const uint32_t w = base + (uint32_t)(i * 64 + lane);
                         if ((sv[i] & kGenBit) != gen) {
                             all = false;
-                            sv[i] = ld64(&bank[w]);
+                            sv[i] = ld64(&bank[A.apart * w]);
                         }
                     }
                     if (__all(all)) break;
@@ -632,7 +632,7 @@ __global__ void k_resident_prep(ResidentArgs A) {
     if (i < 2 * NL) A.rec[i] = A.n0 << 32;
     if (i < A.G)
         for (uint64_t nb = A.n0; nb < A.n0 + 4; ++nb) {
-            if (nb < A.n0 + 2) A.slot[(nb & 1) * A.G + i] = (((nb >> 1) + 1) & 1) << 63;
+            if (nb < A.n0 + 2) A.slot[A.apart * ((nb & 1) * A.G + i)] = (((nb >> 1) + 1) & 1) << 63;
             A.part[(nb & 3) * A.G + i] = (((nb >> 2) + 1) & 1) << 63;
         }
 }
@@ -705,10 +705,15 @@ hipError_t launch_resident(const Geom &g, const ResidentShape &shape, uint64_t n
     A.g = g;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
     // the per-cycle engine's histograms (8 words per line), unused here: two banks of
-    // records, then the slots and the counters (6 words per workgroup, G <= lines)
+    // records, then the counters (4 words per workgroup) and the slots (2, each on a cache
+    // line of its own where there is room for that, else closer; G <= lines).  Side by side
+    // a store took long to arrive through the other workgroups' stores and polls: 7.0 us
+    // per cycle at L = 128, d = 8 against @@.
     A.rec = reinterpret_cast<uint64_t *>(g.hist);
-    A.slot = A.rec + 2 * lines;
-    A.part = A.slot + 2 * (uint64_t)shape.G;
+    A.part = A.rec + 2 * lines;
+    A.slot = A.part + 4 * (uint64_t)shape.G;
+    A.apart = 16;
+    while (A.apart > 1 && (4 + 2 * A.apart) * (uint64_t)shape.G > 6 * lines) A.apart /= 2;
     A.n0 = n0;
     A.ncycles = ncycles;
     A.obs_every = obs_every;

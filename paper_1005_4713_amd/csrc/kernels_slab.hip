@@ -300,6 +300,7 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
     constexpr uint32_t D = kSlabDomains;
     const uint32_t kbase = gid * D;
     const uint32_t nvalid = kbase >= g.K ? 0u : (g.K - kbase < D ? g.K - kbase : D);
+    const uint32_t ss = slot_shift(g);
     const bool recorder = gid == 0;
     const uint64_t n_end = n0 + ncycles;
 
@@ -359,13 +360,13 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
         const bool same = !ALL && n > n0 && s == prev_colour;
         // step 6 of the previous cycle: the flips (and count moves) that octant s can see
         if (ALL && n > n0) {
-            if (!wait_neighbours<BLOCK>(xs, st, sh, G, -1, n)) break;
+            if (!wait_neighbours<BLOCK>(xs, st, sh, G, -1, n, ss)) break;
         } else if (n > n0) {
             int diff = s ^ prev_colour;
             if (diff && !(diff & (diff - 1))) {
                 int a = diff == 1 ? 0 : diff == 2 ? 1 : 2;
                 int dir = 2 * a + ((s >> a) & 1);
-                if (!wait_neighbours<BLOCK>(xs, st, sh, G, dir, n)) break;
+                if (!wait_neighbours<BLOCK>(xs, st, sh, G, dir, n, ss)) break;
             }
         }
         prev_colour = s;
@@ -470,13 +471,13 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
         __syncthreads();
 
         // --- step 2: R_max over all active octants (slot banks as in the re-binning engine)
-        uint64_t *bank = xs.slot + (n & 1) * (uint64_t)G;
+        uint64_t *bank = xs.slot + (((n & 1) * (uint64_t)G) << ss);
         const uint64_t gen = ((n >> 1) & 1) << 63;
         if (tid < 64) {
             double v = 0.0;
             for (uint32_t i = tid; i < D; i += 64) v = fmax(v, sh.rk[i]);
             v = wave_max_nonneg(v);
-            if (tid == 63) st64(&bank[gid], double_to_bits(v) | gen);
+            if (tid == 63) st64(&bank[gid << ss], double_to_bits(v) | gen);
         }
         // --- steps 3, 4 and 4b on the predicted R_max while the maxima travel
         U4 dw;
@@ -525,7 +526,7 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
 #pragma unroll
                 for (int i = 0; i < kSlotsPerLane; ++i) {
                     uint32_t w = base + (uint32_t)i * 64 + tid;
-                    sv[i] = w < G ? ld64(&bank[w]) : gen;
+                    sv[i] = w < G ? ld64(&bank[w << ss]) : gen;
                 }
                 for (;;) {
                     bool all = true;
@@ -534,7 +535,7 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
                         uint32_t w = base + (uint32_t)i * 64 + tid;
                         if ((sv[i] & (1ull << 63)) != gen) {
                             all = false;
-                            sv[i] = ld64(&bank[w]);
+                            sv[i] = ld64(&bank[w << ss]);
                         }
                     }
                     if (__all(all)) break;
@@ -653,14 +654,14 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
         }
         if (tid == 0 && publish_flag) {
             if (record || last) __builtin_amdgcn_s_waitcnt(0);
-            st64(&xs.flag[gid], n + 1);
+            st64(&xs.flag[gid << ss], n + 1);
         }
     }
 
     // end of the launch: workgroup 0 waits for every workgroup, then appends the
     // pending records and the record of the last cycle
     if (recorder) {
-        if (tid < 64 && !sh.abort) wait_all_flags(xs, st, sh, G, tid, n_end);
+        if (tid < 64 && !sh.abort) wait_all_flags(xs, st, sh, G, tid, n_end, ss);
         __syncthreads();
         if (tid < 64 && !sh.abort) {
             while (sh.pend_head != sh.pend_tail) {
@@ -963,7 +964,7 @@ hipError_t launch_slab(const Geom &g, uint64_t n0, uint64_t ncycles, uint32_t ob
     if (!g.sc || g.h != 16) return hipErrorInvalidValue;
     PersistScratch xs = scratch_of(g, grid);
     if (prep) {
-        hipError_t e = launch_persistent_prep(xs, (uint32_t)grid, n0, stream);
+        hipError_t e = launch_persistent_prep(g, xs, (uint32_t)grid, n0, stream);
         if (e != hipSuccess) return e;
     }
     Replica R;

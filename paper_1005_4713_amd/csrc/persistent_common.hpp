@@ -20,14 +20,22 @@ constexpr uint32_t kNoEvent = 0xFFFFFFFFu;
 
 // Device scratch of the persistent engine (its own region of the state).
 struct PersistScratch {
-    uint64_t *slot;     // 2 x G: R_max of each workgroup, generation bit 63
-    uint64_t *flag;     // G: cycles whose flips are complete
+    uint64_t *slot;     // 2 x G: R_max of each workgroup, generation bit 63 (each in its own place, slot_at)
+    uint64_t *flag;     // G: cycles whose flips are complete (likewise)
     int64_t *recp;      // kRecBanks x G x 3: counter partials (fired, dM, dB) since launch start
     int64_t *fin;       // G x 3: each workgroup's totals (fired, dM, dB) at the end of the launch
     uint64_t *emitted;  // records of this launch appended so far (fixed-bound variant); 0 between launches
     double *rpred;      // 8: the last R_max of each colour, the next launch's first predictions
 };
 constexpr uint64_t kScratchWordsPerWg = 2 + 1 + 3 * kRecBanks + 3;
+
+// The slots and flags lie in the histogram region of the state (8 words per line, of no
+// other use to the persistent engines), each on a cache line of its own: a store to a
+// line that other workgroups are storing to and polling took long to arrive (@@).
+// A workgroup has at least 32 lines, so 48 words each fit; a lattice of fewer than six
+// lines has one workgroup and keeps them side by side.
+constexpr uint32_t kSlotShift = 4;
+__host__ __device__ inline uint32_t slot_shift(const Geom &g) { return g.K * g.lpd >= 6 ? kSlotShift : 0u; }
 
 // One lattice of a persistent launch: its geometry and buffers, its sync
 // scratch, the cycles to run, and its range of workgroups in the launch.
@@ -691,14 +699,14 @@ __device__ __forceinline__ void sum_triples(const int64_t *p, uint32_t G, int la
 // error (error set, sh.abort raised).
 template <class SH>
 __device__ __forceinline__ bool wait_all_flags(const PersistScratch &xs, DevState *st, SH &sh, uint32_t G,
-                                               int lane, uint64_t upto) {
+                                               int lane, uint64_t upto, uint32_t ss) {
     const uint64_t start = now_ticks();
     for (uint32_t base = 0; base < G; base += 64 * kWgPerLane) {
         uint64_t fv[kWgPerLane];
 #pragma unroll
         for (int i = 0; i < kWgPerLane; ++i) {
             const uint32_t w = base + (uint32_t)(i * 64 + lane);
-            fv[i] = w < G ? ld64(&xs.flag[w]) : upto;
+            fv[i] = w < G ? ld64(&xs.flag[w << ss]) : upto;
         }
         for (;;) {
             bool done = true;
@@ -706,7 +714,7 @@ __device__ __forceinline__ bool wait_all_flags(const PersistScratch &xs, DevStat
             for (int i = 0; i < kWgPerLane; ++i)
                 if (fv[i] < upto) {
                     done = false;
-                    fv[i] = ld64(&xs.flag[base + (uint32_t)(i * 64 + lane)]);
+                    fv[i] = ld64(&xs.flag[(base + (uint32_t)(i * 64 + lane)) << ss]);
                 }
             if (__all(done)) break;
             __builtin_amdgcn_s_sleep(1);
@@ -762,7 +770,7 @@ __device__ __forceinline__ void emit_record(const Geom &g, const PersistScratch 
 // dir < 0) have completed `upto` cycles; false on a timeout (error set).
 template <int BLOCK, class SH>
 __device__ __forceinline__ bool wait_neighbours(const PersistScratch &xs, DevState *st, SH &sh, uint32_t G,
-                                                int dir, uint64_t upto) {
+                                                int dir, uint64_t upto, uint32_t ss) {
     const int tid = threadIdx.x;
     // the directions' lists laid end to end, one flag per thread: every thread
     // waits on its own flag, so all directions cost one round trip together
@@ -780,7 +788,7 @@ __device__ __forceinline__ bool wait_neighbours(const PersistScratch &xs, DevSta
         }
         const uint32_t w = sh.nbr_cnt[d] > kMaxNbr ? i : sh.nbr[d][i];
         const uint64_t start = now_ticks();
-        while (ld64(&xs.flag[w]) < upto) {
+        while (ld64(&xs.flag[w << ss]) < upto) {
             __builtin_amdgcn_s_sleep(1);
             if (now_ticks() - start > kTimeoutTicks || ld32(&st->error)) {
                 atomicOr(&st->error, kErrFlagTimeout);
@@ -827,7 +835,7 @@ struct RowsGeometry {
 // and its set-up before a launch starting at cycle n0.
 PersistScratch scratch_of(const Geom &g, int G);
 hipError_t launch_resident_grid(const void *kern, int grid, int block, void **args, hipStream_t stream);
-hipError_t launch_persistent_prep(const PersistScratch &xs, uint32_t G, uint64_t n0, hipStream_t stream);
+hipError_t launch_persistent_prep(const Geom &g, const PersistScratch &xs, uint32_t G, uint64_t n0, hipStream_t stream);
 
 // The neighbour workgroups of this workgroup per direction, from the bitmap
 // sh.nbr_bits (one thread per direction, a word of the bitmap at a time).

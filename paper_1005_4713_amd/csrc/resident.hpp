@@ -19,12 +19,13 @@ struct ResidentShape {
 struct ResidentArgs {
     Geom g;
     uint64_t *rec;   // 2 x lines: the event of each line, cycle + 1 in the upper half
-    uint64_t *slot;  // 2 x G: R_max of each workgroup, generation bit 63
+    uint64_t *slot;  // 2 x G, `apart` words apart: R_max of each workgroup, generation bit 63
     uint64_t *part;  // 4 x G: counters of a cycle of each workgroup, generation bit 63
     uint64_t n0, ncycles;
     uint32_t obs_every, G, D;
     uint32_t ow, W;  // words (of four sites) per octant, and per lane of a line's group
     uint32_t hinv;   // ceil(2^32 / h)
+    uint32_t apart;
 };
 
 bool resident_configure(const Geom &g, ResidentShape &out);

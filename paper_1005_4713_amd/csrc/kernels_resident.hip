@@ -6,9 +6,9 @@
 // than one workgroup, the R_max exchange); it reads nothing from memory but
 // other workgroups' words.  Per cycle, records included, against the three
 // launches per cycle it replaces: L = 16, d = 8 (one workgroup) 2.7 us against
-// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 7.0 us against 77, of
+// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 5.7 us against 77, of
 // which binning took 49 (a workgroup per line of 64 sites); L = 72, d = 8, two
-// colours 6.5 us against 58.
+// colours 5.2 us against 58.
 //
 // Layout in LDS, per domain of the workgroup:
 //   * one byte per site, octant-major in canonical order: 8 [up] + (up
@@ -708,7 +708,7 @@ hipError_t launch_resident(const Geom &g, const ResidentShape &shape, uint64_t n
     // records, then the counters (4 words per workgroup) and the slots (2, each on a cache
     // line of its own where there is room for that, else closer; G <= lines).  Side by side
     // a store took long to arrive through the other workgroups' stores and polls: 7.0 us
-    // per cycle at L = 128, d = 8 against @@.
+    // per cycle at L = 128, d = 8 against 5.7 here.
     A.rec = reinterpret_cast<uint64_t *>(g.hist);
     A.part = A.rec + 2 * lines;
     A.slot = A.part + 4 * (uint64_t)shape.G;

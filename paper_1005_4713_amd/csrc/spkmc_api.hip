@@ -473,10 +473,14 @@ struct HeaderPlaces {
         if (!tried) {
             tried = true;
             void *p = nullptr;
+            // a capture in another thread, or in this one, is not disturbed
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
             if (hipHostMalloc(&p, kPlaces * sizeof(DevState), hipHostMallocPortable) == hipSuccess)
                 host = static_cast<DevState *>(p);
             else
                 (void)hipGetLastError();
+            if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
         }
         if (!host || used == ~0ull) return nullptr;
         const int i = __builtin_ctzll(~used);

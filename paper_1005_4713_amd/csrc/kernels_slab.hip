@@ -36,7 +36,10 @@ struct SlabShared {
     double r[14];
     alignas(16) uint32_t oct[kSlabDomains][kOctLds];    // active octants and their halos
     uint32_t sc[kSlabDomains][kSlabWords];  // slab counts of the active octants
-    uint16_t cnt[kSlabDomains][8][14];      // class counts (the active octant; every octant for the all-octant R_max)
+    // class counts: of the active octant (place 0) and, for the all-octant R_max, of the
+    // octants that the previous cycle's flips lay in or next to (places 1 .. 4)
+    uint16_t cnt[kSlabDomains][5][14];
+    double rko[kSlabDomains][8];            // all-octant R_max: every octant's line
     double acc[kSlabDomains][14];           // running FP64 sums of the frequency lines
     double rk[kSlabDomains];
     alignas(16) uint32_t zbuf[kSlabRows][kRowHalo];     // binning at launch start: halo faces per row
@@ -59,6 +62,10 @@ struct SlabShared {
 __device__ __forceinline__ void st32(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+// The all-octant R_max: the octant of count place 1 .. 4 after flips of colour `flipped`,
+// that octant itself and the three that share a face with it.
+__device__ __forceinline__ int slab_place_octant(int flipped, int place) { return flipped ^ ((1 << place) >> 2); }
 
 // Spin (1 = up) of the active octant at local (x, y, z), each in [-1, 16] and
 // at most one outside [0, 16): the octant's words or one of its halo faces.
@@ -338,6 +345,25 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
     for (int o = 0; o < 8; ++o) slab_bin_octant(g, kbase, nvalid, o, sh);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
+    if (ALL) {
+        // every octant's line at launch start; in the loop only those that a cycle's
+        // flips may have moved are taken again
+        for (uint32_t i = tid; i < D * 8; i += nthr) {
+            const uint32_t ld = i >> 3;
+            double a = 0.0;
+            if (ld < nvalid) {
+                const uint32_t *w = g.sc + ((uint64_t)(kbase + ld) * 8 + (i & 7u)) * kSlabWords;
+                for (int c = 0; c < 14; ++c) {
+                    const uint64_t v = ld_words2(w + 2 * c);
+                    const uint32_t w0 = (uint32_t)v, w1 = (uint32_t)(v >> 32);
+                    const double term = (double)((w0 & 0xFFFFu) + (w0 >> 16) + (w1 & 0xFFFFu) + (w1 >> 16)) * sh.r[c];
+                    a = a + term;
+                }
+            }
+            sh.rko[ld][i & 7u] = a;
+        }
+        __syncthreads();
+    }
 
     DevState *st = g.st;
     // launch-start totals: during a launch only the recorder writes them, at
@@ -369,6 +395,13 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
                 if (!wait_neighbours<BLOCK>(xs, st, sh, G, dir, n, ss)) break;
             }
         }
+        // With ALL: the places whose lines are taken this cycle.  The flips of colour
+        // `flipped` moved counts of that octant and of the three that share a face
+        // with it (in this domain or the next), places 1 .. 4; the active octant has
+        // place 0 unless it is one of them.
+        const int flipped = prev_colour;
+        const bool fresh = flipped < 0;  // the launch's first cycle: every line is current
+        const bool active_in = !fresh && __popc((uint32_t)(s ^ flipped)) <= 1;
         prev_colour = s;
 
         // --- step 1 from the counts: the slab counts of the active octants first
@@ -382,8 +415,9 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
             // with ALL this cycle reads back the counts of the previous cycle's
             // octant, which this workgroup stored: those stores complete first
             if (ALL) __builtin_amdgcn_s_waitcnt(0);
-            // lane c of a row: class c's slab counts (of every octant with ALL)
-            constexpr int NO = ALL ? 8 : 1;
+            // lane c of a row: class c's slab counts of each place (with ALL;
+            // all eight octants, every cycle: 19.95 us a cycle of 1024^3 instead of 18.2)
+            constexpr int NO = ALL ? 5 : 1;
             uint32_t scw[P][NO][2];
 #pragma unroll
             for (int pp = 0; pp < P; ++pp) {
@@ -391,8 +425,9 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
                 const bool valid = ld < nvalid;
 #pragma unroll
                 for (int oi = 0; oi < NO; ++oi) {
-                    const uint32_t o = ALL ? (uint32_t)oi : (uint32_t)s;
-                    const int off = valid && l < 14
+                    const uint32_t o = (uint32_t)(oi == 0 ? s : slab_place_octant(flipped, oi));
+                    const bool taken = !ALL || (oi == 0 ? !active_in : !fresh);
+                    const int off = valid && l < 14 && taken
                                         ? (int)((((kbase + ld) * 8u + o) * kSlabWords + 2u * (uint32_t)l) * 4u)
                                         : endSC;
                     const auto v = __builtin_amdgcn_raw_buffer_load_b64(SC, off, 0, kCoherent);
@@ -409,9 +444,8 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
 #pragma unroll
                     for (int oi = 0; oi < NO; ++oi) {
                         const uint32_t w0 = scw[pp][oi][0], w1 = scw[pp][oi][1];
-                        const int o = ALL ? oi : s;
-                        sh.cnt[ld][o][l] = (uint16_t)((w0 & 0xFFFFu) + (w0 >> 16) + (w1 & 0xFFFFu) + (w1 >> 16));
-                        if (o == s) {
+                        sh.cnt[ld][oi][l] = (uint16_t)((w0 & 0xFFFFu) + (w0 >> 16) + (w1 & 0xFFFFu) + (w1 >> 16));
+                        if (oi == 0 ? !(ALL && active_in) : active_in && slab_place_octant(flipped, oi) == s) {
                             sh.sc[ld][2 * l] = w0;
                             sh.sc[ld][2 * l + 1] = w1;
                         }
@@ -435,33 +469,30 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
                 const uint32_t ld = (uint32_t)(pp * rows + row);
                 if (l < 14) {
                     const uint32_t v0 = sh.sc[ld][2 * l], v1 = sh.sc[ld][2 * l + 1];
-                    sh.cnt[ld][s][l] = (uint16_t)((v0 & 0xFFFFu) + (v0 >> 16) + (v1 & 0xFFFFu) + (v1 >> 16));
+                    sh.cnt[ld][0][l] = (uint16_t)((v0 & 0xFFFFu) + (v0 >> 16) + (v1 & 0xFFFFu) + (v1 >> 16));
                 }
             }
         }
-        if (ALL && tid < (int)D) sh.rk[tid] = 0.0;
         __syncthreads();
         if (ALL) {
-            // every octant's frequency line; the active one keeps its running sums,
-            // the domain's largest line goes into rk (non-negative doubles order as
-            // their bit patterns)
-            for (uint32_t i = tid; i < D * 8; i += nthr) {
-                const uint32_t ld = i >> 3;
-                const int o = (int)(i & 7u);
+            // the places' frequency lines; the active octant keeps its running sums
+            const uint32_t first = active_in ? 1u : 0u, places = fresh ? 1u : 5u;
+            for (uint32_t i = tid + first * D; i < places * D; i += nthr) {
+                const uint32_t ld = i % D, pl = i / D;
+                const int o = pl == 0 ? s : slab_place_octant(flipped, (int)pl);
                 double a = 0.0;
                 for (int c = 0; c < 14; ++c) {
-                    double term = (double)sh.cnt[ld][o][c] * sh.r[c];
+                    double term = (double)sh.cnt[ld][pl][c] * sh.r[c];
                     a = a + term;
                     if (o == s) sh.acc[ld][c] = a;
                 }
-                if (ld < nvalid)
-                    atomicMax(reinterpret_cast<unsigned long long *>(&sh.rk[ld]), (unsigned long long)double_to_bits(a));
+                sh.rko[ld][o] = a;  // 0 where there is no domain
             }
         } else {
             for (uint32_t i = tid; i < D; i += nthr) {
                 double a = 0.0;
                 for (int c = 0; c < 14; ++c) {
-                    double term = (double)sh.cnt[i][s][c] * sh.r[c];
+                    double term = (double)sh.cnt[i][0][c] * sh.r[c];
                     a = a + term;
                     sh.acc[i][c] = a;
                 }
@@ -475,7 +506,13 @@ __device__ __forceinline__ void slab_body(const Replica &R, const uint32_t gid, 
         const uint64_t gen = ((n >> 1) & 1) << 63;
         if (tid < 64) {
             double v = 0.0;
-            for (uint32_t i = tid; i < D; i += 64) v = fmax(v, sh.rk[i]);
+            if (ALL) {
+                const double *rko = &sh.rko[0][0];
+#pragma unroll
+                for (uint32_t i = 0; i < D * 8; i += 64) v = fmax(v, rko[i + tid]);
+            } else {
+                for (uint32_t i = tid; i < D; i += 64) v = fmax(v, sh.rk[i]);
+            }
             v = wave_max_nonneg(v);
             if (tid == 63) st64(&bank[gid << ss], double_to_bits(v) | gen);
         }

@@ -37,7 +37,7 @@ uint64_t persistent_scratch_words(uint64_t K);
 // Slab engine (PACKED, octant edge 16, variant 0): support, launch shape, launch.
 bool slab_supported(const Geom &g, const spkmc_params &p, std::string &why);
 hipError_t slab_configure(const Geom &g, int &grid, int &block, int &wg_domains);
-hipError_t launch_slab(const Geom &g, uint64_t n0, uint64_t ncycles, uint32_t obs_every, int grid, bool prep,
+hipError_t launch_slab(const Geom &g, uint64_t n0, uint64_t ncycles, uint32_t obs_every, int grid, bool prep, bool counted,
                        hipStream_t stream);
 struct Replica;
 size_t replica_bytes();
@@ -72,7 +72,7 @@ struct spkmc_ctx {
     // primed_span (cycles run since their last set-up) is at least 2
     int primed_grid;
     uint64_t primed_cycle, primed_span;
-    // the slab counts in the state belong to the spins (per-cycle slab kernels)
+    // the slab counts in the state belong to the spins (slab engine, per-cycle slab kernels)
     bool counts_current;
     int engine;
     spkmc::ResidentShape res;      // CYCLE engine: the on-chip launch, where the lattice fits

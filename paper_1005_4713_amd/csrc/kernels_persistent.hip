@@ -1061,7 +1061,7 @@ hipError_t launch_persistent(const Geom &g, uint64_t n0, uint64_t ncycles, uint3
     R.obs_every = obs_every;
     R.first_wg = 0;
     R.G = (uint32_t)grid;
-    R.pad = 0;
+    R.counted = 0;
     void *args[] = {&R};
     return launch_resident_grid(kern, grid, block, args, stream);
 }
@@ -1118,7 +1118,7 @@ hipError_t batch_plan(const Geom *const *gs, const uint64_t *n0, const uint64_t 
         out[i].ncycles = ncycles[i];
         out[i].obs_every = obs_every;
         out[i].first_wg = first;
-        out[i].pad = 0;
+        out[i].counted = 0;
         first += out[i].G;
     }
     const uint32_t cap = batch_capacity(h, P, lpd);

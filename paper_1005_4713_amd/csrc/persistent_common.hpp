@@ -47,7 +47,7 @@ struct Replica {
     uint64_t n0, ncycles;
     uint32_t obs_every;
     uint32_t first_wg, G;  // workgroups first_wg .. first_wg + G - 1 run this lattice
-    uint32_t pad;
+    uint32_t counted;      // slab engine: the slab counts in the state belong to the spins
 };
 
 namespace {

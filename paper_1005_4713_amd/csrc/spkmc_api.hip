@@ -413,8 +413,10 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
         // the set-up of the sync words is needed unless the previous launch left
         // them ready for this one
         const bool primed = c->primed_grid == c->grid && c->primed_cycle == c->cycle && c->primed_span >= 2;
+        const bool current = c->counts_current;
+        c->counts_current = false;
         if (c->engine == SPKMC_ENGINE_SLAB)
-            e = launch_slab(c->g, c->cycle, ncycles, obs_every, c->grid, !primed, c->stream);
+            e = launch_slab(c->g, c->cycle, ncycles, obs_every, c->grid, !primed, current, c->stream);
         else
             e = launch_persistent(c->g, c->cycle, ncycles, obs_every, c->grid, c->block, c->wg_domains,
                                   c->engine == SPKMC_ENGINE_INCREMENTAL, !primed, c->stream);
@@ -422,6 +424,7 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
             c->primed_grid = 0;
             return hip_fail(c, e, c->engine == SPKMC_ENGINE_SLAB ? "slab kernel launch" : "persistent kernel launch");
         }
+        c->counts_current = c->engine == SPKMC_ENGINE_SLAB;
         c->primed_span = (primed ? c->primed_span : 0) + ncycles;
         c->primed_grid = c->grid;
         c->cycle += ncycles;

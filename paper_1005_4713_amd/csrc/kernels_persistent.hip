@@ -509,7 +509,16 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         auto line_count = [&](uint32_t ld, int c) -> uint32_t {
             return INC ? hcount(sh.histp[ld][s], c) : sh.hist[ld][c];
         };
-        uint32_t cpred = 0;  // per pass: predicted class + 1, five bits each
+        uint32_t cpred = 0;  // per pass: predicted class + 1, five bits each (row-wise verification)
+        // The verification a lane per line (one of the wavefront's 16): the line's uniform
+        // and the running sums on either side of its class, read before the poll, so that
+        // mostly one comparison is left after it.  1024^3, four passes of octant edge 16:
+        // 12.07 us per cycle row by row, 11.83 so.  With one or two passes a row-wise
+        // check is as short and starts later: 512^3 6.41 us so against 6.43, the replica
+        // batch (two passes of octant edge 8, registers full) 3.47 ms against 3.52.
+        constexpr bool kLaneCheck = H == 16 && P == 4 && RND == 1;
+        const uint32_t vl = (((uint32_t)tid >> 2) & (uint32_t)(P - 1)) * (uint32_t)rows + ((uint32_t)tid >> 6) * 4u + ((uint32_t)tid & 3u);
+        double vu = 0.0, vlo = 0.0, vhi = 0.0;
         if constexpr (RND == 1) {
             const double Rspec = bound ? rbound : sh.rpred[s];
 #pragma unroll
@@ -529,8 +538,15 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                     uz = sh.usite[ld];
                 }
                 const int cs = row_class(sh.acc[ld], ld < nvalid, u * Rspec, l, row);
-                cpred |= (uint32_t)(cs + 1) << (5 * pp);
+                if constexpr (!kLaneCheck) cpred |= (uint32_t)(cs + 1) << (5 * pp);
                 select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, uz, l, &sh.selq[ld], st);
+            }
+            if (kLaneCheck && !bound) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                vu = sh.uline[vl];
+                class_limits(sh.acc[vl], sh.selq[vl], vlo, vhi);
             }
         }
 
@@ -589,17 +605,16 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         s_next = sh.next_colour;
 
         if constexpr (RND > 1) {
-            // wide mode: the lines whose class differs under the true R_max, a row each
-            // (the selected class is in the line's slot)
+            // wide mode: the lines whose class differs under the true R_max
+            // (the selected class is in the line's slot), then selected again, a row each
             if (!bound) {
                 if (tid == 0) sh.rpred[s] = Rmax;
-#pragma unroll 4
-                for (int j = 0; j < P * RND; ++j) {
-                    const uint32_t ld = (uint32_t)(j * rows + row);
-                    const int cs = row_class(sh.acc[ld], ld < nvalid, sh.uline[ld] * Rmax, l, row);
-                    const uint32_t f = sh.selq[ld];
-                    if (l == 0 && cs != (f == kNoEvent ? -1 : (int)(f >> 12)))
-                        sh.redo[atomicAdd(&sh.nredo, 1u)] = (uint16_t)ld;
+                // (a thread per line; a row per line: 1024^3 with two colours 47.8 us per
+                // cycle instead of 45.5)
+                for (uint32_t ld = tid; ld < nvalid; ld += nthr) {
+                    double lo, hi;
+                    class_limits(sh.acc[ld], sh.selq[ld], lo, hi);
+                    if (outside_class(sh.uline[ld] * Rmax, lo, hi)) sh.redo[atomicAdd(&sh.nredo, 1u)] = (uint16_t)ld;
                 }
                 __syncthreads();
                 const uint32_t nredo = sh.nredo;
@@ -617,12 +632,21 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         } else if (!bound) {
             // the true R_max: rows whose class differs select again
             if (tid == 0) sh.rpred[s] = Rmax;
+            if (!kLaneCheck || __any(vl < nvalid && outside_class(vu * Rmax, vlo, vhi))) {
 #pragma unroll
-            for (int pp = 0; pp < P; ++pp) {
-                const uint32_t ld = (uint32_t)(pp * rows + row);
-                const int cs = row_class(sh.acc[ld], ld < nvalid, sh.uline[ld] * Rmax, l, row);
-                if ((uint32_t)(cs + 1) != ((cpred >> (5 * pp)) & 31u))
-                    select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, sh.usite[ld], l, &sh.selq[ld], st);
+                for (int pp = 0; pp < P; ++pp) {
+                    const uint32_t ld = (uint32_t)(pp * rows + row);
+                    const int cs = row_class(sh.acc[ld], ld < nvalid, sh.uline[ld] * Rmax, l, row);
+                    uint32_t before;  // the predicted class + 1
+                    if constexpr (kLaneCheck) {
+                        const uint32_t f = sh.selq[ld];
+                        before = f == kNoEvent ? 0u : (f >> 12) + 1u;
+                    } else {
+                        before = (cpred >> (5 * pp)) & 31u;
+                    }
+                    if ((uint32_t)(cs + 1) != before)
+                        select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, sh.usite[ld], l, &sh.selq[ld], st);
+                }
             }
         }
         __syncthreads();

@@ -565,6 +565,16 @@ __device__ __forceinline__ int row_class(const double *acc, bool valid, double t
     return rowbits ? __builtin_ctz(rowbits) : -1;
 }
 
+// The running sums between which a target keeps a line's selected event f (the class
+// in its upper bits, or kNoEvent): its class's own sum and the one before.
+__device__ __forceinline__ void class_limits(const double *acc, uint32_t f, double &lo, double &hi) {
+    const uint32_t c = f == kNoEvent ? 14u : f >> 12;
+    const double below = acc[c ? c - 1 : 0], own = acc[c < 14 ? c : 13];
+    lo = c ? below : 0.0;
+    hi = c < 14 ? own : __builtin_inf();
+}
+__device__ __forceinline__ bool outside_class(double target, double lo, double hi) { return !(target < hi) || target < lo; }
+
 // The event of a row for class cs with ncs sites: the j-th site of the class in
 // canonical order (j from the uniform uz), written into the row's selection slot
 // as (cs << 12) | q, or kNoEvent.  Every lane of the row takes part.

@@ -152,7 +152,8 @@ __device__ __forceinline__ uint32_t row_lane(uint32_t v, int j) {
 // takes its registers.  Once the true R_max is known the few lines whose class
 // it changes (0.3 %) are gathered, and a row each loads, classifies and selects
 // them again.  Deriving every line's planes a second time for a selection with
-// the true R_max took 59 us per cycle for two colours at 1024^3, this 49.  (Rounds
+// the true R_max took 59 us per cycle for two colours at 1024^3, this 49 and, with the slots
+// apart and a thread per line after the exchange, 45.5.  (Rounds
 // of two passes with the next round's words in flight: 56; four passes with the
 // next round's first in flight: 49, and the register file spills.)
 // BND: 1 when the lattice may run with the fixed bound (read from the variant at
@@ -516,10 +517,33 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         // 12.07 us per cycle row by row, 11.83 so.  With one or two passes a row-wise
         // check is as short and starts later: 512^3 6.41 us so against 6.43, the replica
         // batch (two passes of octant edge 8, registers full) 3.47 ms against 3.52.
-        constexpr bool kLaneCheck = H == 16 && P == 4 && RND == 1;
-        const uint32_t vl = (((uint32_t)tid >> 2) & (uint32_t)(P - 1)) * (uint32_t)rows + ((uint32_t)tid >> 6) * 4u + ((uint32_t)tid & 3u);
+        constexpr bool kLaneCheck = H == 16 && P == 4 && RND == 1 && !INC;
+        const uint32_t vl = (((uint32_t)l >> 2) & (uint32_t)(P - 1)) * (uint32_t)rows + (uint32_t)row;
         double vu = 0.0, vlo = 0.0, vhi = 0.0;
-        if constexpr (RND == 1) {
+        if constexpr (kLaneCheck) {
+            // class and rank of the wavefront's 16 lines by four lanes each: a quarter of
+            // the running sums per lane, the classes whose sum the target has reached
+            // counted over the four.  1024^3: 11.70 us per cycle, 11.81 with a ballot per
+            // pass and row.
+            const double Rspec = bound ? rbound : sh.rpred[s];
+            vu = sh.uline[vl];
+            const double target = vu * Rspec;
+            const double *acc = sh.acc[vl];
+            uint32_t c = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ci = 4 * (l & 3) + i;
+                c += ci < 14 && !(target < acc[ci < 14 ? ci : 13]) ? 1u : 0u;
+            }
+            c = quad_total(c);
+            if (vl >= nvalid) c = 14;
+            const uint32_t e = pack_event(c, mul_index(sh.usite[vl], c < 14 ? sh.hist[vl][c] : 0u));
+            vlo = c ? acc[c - 1] : 0.0;
+            vhi = c < 14 ? acc[c] : __builtin_inf();
+#pragma unroll
+            for (int pp = 0; pp < P; ++pp)
+                place_packed<H>(pl[pp], bcast_quad(e, pp), l, &sh.selq[pp * rows + row], st);
+        } else if constexpr (RND == 1) {
             const double Rspec = bound ? rbound : sh.rpred[s];
 #pragma unroll
             for (int pp = 0; pp < P; ++pp) {
@@ -538,15 +562,8 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                     uz = sh.usite[ld];
                 }
                 const int cs = row_class(sh.acc[ld], ld < nvalid, u * Rspec, l, row);
-                if constexpr (!kLaneCheck) cpred |= (uint32_t)(cs + 1) << (5 * pp);
+                cpred |= (uint32_t)(cs + 1) << (5 * pp);
                 select_site<H>(pl[pp], cs, cs >= 0 ? line_count(ld, cs) : 0u, uz, l, &sh.selq[ld], st);
-            }
-            if (kLaneCheck && !bound) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                vu = sh.uline[vl];
-                class_limits(sh.acc[vl], sh.selq[vl], vlo, vhi);
             }
         }
 

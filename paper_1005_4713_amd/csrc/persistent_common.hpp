@@ -122,6 +122,21 @@ __device__ __forceinline__ uint32_t bcast_lane(uint32_t v, int lane) {  // lane 
     }
 }
 
+__device__ __forceinline__ uint32_t bcast_quad(uint32_t v, int quad) {  // lane 4 quad of each row (folds when unrolled)
+    switch (quad) {
+        case 0: return bcast<kRowBcast + 0>(v);
+        case 1: return bcast<kRowBcast + 4>(v);
+        case 2: return bcast<kRowBcast + 8>(v);
+        default: return bcast<kRowBcast + 12>(v);
+    }
+}
+// Sum over each group of four lanes, in all four.
+__device__ __forceinline__ uint32_t quad_total(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);  // lanes 1 0 3 2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);  // lanes 2 3 0 1
+    return v;
+}
+
 __device__ __forceinline__ uint32_t align_hi(uint32_t hi, uint32_t lo, uint32_t s) {
     return __builtin_amdgcn_alignbit(hi, lo, s);  // ({hi, lo} >> s)[31:0]
 }
@@ -575,21 +590,14 @@ __device__ __forceinline__ void class_limits(const double *acc, uint32_t f, doub
 }
 __device__ __forceinline__ bool outside_class(double target, double lo, double hi) { return !(target < hi) || target < lo; }
 
-// The event of a row for class cs with ncs sites: the j-th site of the class in
-// canonical order (j from the uniform uz), written into the row's selection slot
-// as (cs << 12) | q, or kNoEvent.  Every lane of the row takes part.
+// The event of a row: the j-th site of class cs in canonical order, written into the
+// row's selection slot as (cs << 12) | q, or kNoEvent where `any` is false.  The class
+// as the patterns that its sites' planes equal (ps spin, p0 .. p2 up neighbours).
+// Every lane of the row takes part.
 template <int H>
-__device__ __forceinline__ void select_site(const Planes<H> &pl, int cs, uint32_t ncs, uint32_t uz, int l,
-                                            uint32_t *slot, DevState *st) {
+__device__ __forceinline__ void place_event(const Planes<H> &pl, bool any, uint32_t cs, uint32_t j, uint32_t ps, uint32_t p0,
+                                            uint32_t p1, uint32_t p2, int l, uint32_t *slot, DevState *st) {
     constexpr int WPL = Planes<H>::W;
-    if (l == 0) *slot = kNoEvent;
-    const uint32_t j = cs >= 0 ? mul_index(uz, ncs) : 0u;
-    // class cs as (spin, n_up pattern): up spin (cs >= 7): n_up = cs - 7; down
-    // spin: n_up = 6 - cs.  A row without an event never uses its masks.
-    const int up = cs >= 7, v = up ? cs - 7 : 6 - cs;
-    const uint32_t ps = up ? 0xFFFFFFFFu : 0u;  // the pattern each plane must equal
-    const uint32_t p0 = (v & 1) ? 0xFFFFFFFFu : 0u, p1 = (v & 2) ? 0xFFFFFFFFu : 0u;
-    const uint32_t p2 = (v & 4) ? 0xFFFFFFFFu : 0u;
     uint32_t mk[WPL], cum[WPL];
     uint32_t cnt = 0;
 #pragma unroll
@@ -605,8 +613,8 @@ __device__ __forceinline__ void select_site(const Planes<H> &pl, int cs, uint32_
     // inclusive prefix over the 16 lanes of the row (canonical order = lane order)
     const uint32_t incl = row_scan(cnt);
     const uint32_t excl = incl - cnt;
-    if (cs >= 0 && l == 15 && j >= incl) atomicOr(&st->error, kErrSelect);  // counts disagree with masks
-    if (cs >= 0 && j >= excl && j < incl) {
+    if (any && l == 15 && j >= incl) atomicOr(&st->error, kErrSelect);  // counts disagree with masks
+    if (any && j >= excl && j < incl) {
         // the word holding the target: as many words as have running counts not
         // above its rank; then its rank inside that word
         const uint32_t r0 = j - excl;
@@ -637,8 +645,39 @@ __device__ __forceinline__ void select_site(const Planes<H> &pl, int cs, uint32_
                 }
         }
         const uint32_t q = (uint32_t)(l * WPL) * 32 + wsel * 32 + (uint32_t)nth_set_bit(msk, r0 - before);
-        *slot = ((uint32_t)cs << 12) | q;  // after lane 0's store, same wavefront
+        *slot = (cs << 12) | q;  // after lane 0's store, same wavefront
     }
+}
+
+// The event of a row for class cs with ncs sites: the site's rank from the uniform uz.
+template <int H>
+__device__ __forceinline__ void select_site(const Planes<H> &pl, int cs, uint32_t ncs, uint32_t uz, int l,
+                                            uint32_t *slot, DevState *st) {
+    if (l == 0) *slot = kNoEvent;
+    const uint32_t j = cs >= 0 ? mul_index(uz, ncs) : 0u;
+    // class cs as (spin, n_up pattern): up spin (cs >= 7): n_up = cs - 7; down
+    // spin: n_up = 6 - cs.  A row without an event never uses its masks.
+    const int up = cs >= 7, v = up ? cs - 7 : 6 - cs;
+    const uint32_t ps = up ? 0xFFFFFFFFu : 0u;  // the pattern each plane must equal
+    const uint32_t p0 = (v & 1) ? 0xFFFFFFFFu : 0u, p1 = (v & 2) ? 0xFFFFFFFFu : 0u;
+    const uint32_t p2 = (v & 4) ? 0xFFFFFFFFu : 0u;
+    place_event<H>(pl, cs >= 0, (uint32_t)cs, j, ps, p0, p1, p2, l, slot, st);
+}
+
+// A line's class and site rank in one word, for place_event: the rank in bits 0 .. 12
+// (kNoRank: the null event), the class in bits 13 .. 16, its patterns ps, p0 .. p2 in
+// bits 17 .. 20.
+constexpr uint32_t kNoRank = 0x1FFFu;  // above every rank of an octant of 16^3 sites
+__device__ __forceinline__ uint32_t pack_event(uint32_t c, uint32_t rank) {  // c = 14: the null event
+    const uint32_t up = c >= 7 ? 1u : 0u, v = up ? c - 7u : 6u - c;
+    return (c >= 14u ? kNoRank : rank) | c << 13 | up << 17 | v << 18;
+}
+template <int H>
+__device__ __forceinline__ void place_packed(const Planes<H> &pl, uint32_t e, int l, uint32_t *slot, DevState *st) {
+    if (l == 0) *slot = kNoEvent;
+    const uint32_t j = e & kNoRank;
+    auto all = [&](int b) { return (uint32_t)__builtin_amdgcn_sbfe((int)e, b, 1); };  // bit b in every bit
+    place_event<H>(pl, j != kNoRank, (e >> 13) & 15u, j, all(17), all(18), all(19), all(20), l, slot, st);
 }
 
 // Flip site q of octant (k, so): its spin word, and the halo copy of every

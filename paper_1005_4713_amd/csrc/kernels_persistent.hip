@@ -142,11 +142,6 @@ __device__ __forceinline__ void bin_all(const Geom &g, uint32_t kbase, uint32_t 
 // neighbours change class, step 6); the active octant is classified only to
 // find the selected site, while the R_max exchange is in flight.
 // INC = false: the active octant of every domain is binned afresh each cycle.
-// Lane j (0..15) of this thread's 16-lane row, for a j known only at run time.
-__device__ __forceinline__ uint32_t row_lane(uint32_t v, int j) {
-    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(((threadIdx.x & 48u) + (uint32_t)j) << 2), (int)v);
-}
-
 // RND > 1 (the wide mode, re-binning engine only): each row runs RND rounds of P
 // lines, each binned and selected on the predicted R_max before the next round
 // takes its registers.  Once the true R_max is known the few lines whose class
@@ -281,6 +276,26 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
             const uint32_t kd = kbase + (uint32_t)((l < P * RND ? l : 0) * rows + row);
             dw = philox10((uint32_t)n, (uint32_t)(n >> 32), line_dom(kd), (uint32_t)line_oct(kd, s), g.seed);
         };
+        // A line's event for the target u R on four lanes (l & 3 of them): a quarter of the
+        // running sums per lane, the classes whose sum the target has reached counted over
+        // the four.  A wavefront does its 16 lines at once.  1024^3: 11.65 us per cycle,
+        // 11.81 with a ballot per pass and row; two colours 44.2 and 45.3.
+        auto line_event = [&](uint32_t ld, double R, double &u, double &lo, double &hi) -> uint32_t {
+            u = sh.uline[ld];
+            const double target = u * R;
+            const double *acc = sh.acc[ld];
+            uint32_t c = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ci = 4 * (l & 3) + i;
+                c += ci < 14 && !(target < acc[ci < 14 ? ci : 13]) ? 1u : 0u;
+            }
+            c = quad_total(c);
+            if (ld >= nvalid) c = 14;
+            lo = c ? acc[c - 1] : 0.0;
+            hi = c < 14 ? acc[c] : __builtin_inf();
+            return pack_event(c, mul_index(sh.usite[ld], c < 14 ? sh.hist[ld][c] : 0u));
+        };
         if constexpr (INC) {
             // --- fold the class changes other workgroups pushed into octant s (and,
             // every kFoldAll cycles, into all octants)
@@ -328,6 +343,17 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
             // moments, the frequency lines, and the selection on the predicted R_max
             const double Rspec = bound ? rbound : sh.rpred[s];
             constexpr uint32_t DR = (uint32_t)(rows * P);  // lines of a round
+            auto draw_lines = [&]() {  // lane j of a row draws for the row's j-th line
+                draw();
+                if (l < P * RND) {
+                    sh.uline[l * rows + row] = unit53(dw.x, dw.y);
+                    sh.usite[l * rows + row] = dw.z;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                drawn = true;
+            };
 #pragma unroll 1
             for (int r = 0; r < RND; ++r) {
                 Raw<H> raw[P];
@@ -356,10 +382,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                     }
                 }
                 __syncthreads();
-                if (!drawn && (uint32_t)(tid & ~63) >= DR) {  // no line of this wavefront to histogram
-                    draw();
-                    drawn = true;
-                }
+                if (!drawn && (uint32_t)(tid & ~63) >= DR) draw_lines();  // no line of this wavefront to histogram
                 for (uint32_t i = tid; i < DR; i += nthr) {
                     const uint32_t ld = (uint32_t)r * DR + i;
                     uint32_t mm[13], hc[14], w[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -384,21 +407,12 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
                     sh.rk[ld] = ld < nvalid ? a : 0.0;
                 }
                 __syncthreads();
-                if (!drawn) draw();
-                drawn = true;
+                if (!drawn) draw_lines();
+                double u, lo, hi;
+                const uint32_t e = line_event((uint32_t)(r * P + (l >> 2)) * (uint32_t)rows + (uint32_t)row, Rspec, u, lo, hi);
 #pragma unroll
-                for (int pp = 0; pp < P; ++pp) {
-                    const int j = r * P + pp;
-                    const uint32_t ld = (uint32_t)(j * rows + row);
-                    const uint32_t ux = row_lane(dw.x, j), uy = row_lane(dw.y, j), uz = row_lane(dw.z, j);
-                    const double u = unit53(ux, uy);
-                    if (l == 0) {
-                        sh.uline[ld] = u;
-                        sh.usite[ld] = uz;
-                    }
-                    const int cs = row_class(sh.acc[ld], ld < nvalid, u * Rspec, l, row);
-                    select_site<H>(pl[pp], cs, cs >= 0 ? sh.hist[ld][cs] : 0u, uz, l, &sh.selq[ld], st);
-                }
+                for (int pp = 0; pp < P; ++pp)
+                    place_packed<H>(pl[pp], bcast_quad(e, pp), l, &sh.selq[(r * P + pp) * rows + row], st);
             }
         } else {
             // --- steps 1 and 4a: class planes and moments of the active octants
@@ -521,25 +535,7 @@ __device__ __forceinline__ void persistent_body(const Replica &R, const uint32_t
         const uint32_t vl = (((uint32_t)l >> 2) & (uint32_t)(P - 1)) * (uint32_t)rows + (uint32_t)row;
         double vu = 0.0, vlo = 0.0, vhi = 0.0;
         if constexpr (kLaneCheck) {
-            // class and rank of the wavefront's 16 lines by four lanes each: a quarter of
-            // the running sums per lane, the classes whose sum the target has reached
-            // counted over the four.  1024^3: 11.70 us per cycle, 11.81 with a ballot per
-            // pass and row.
-            const double Rspec = bound ? rbound : sh.rpred[s];
-            vu = sh.uline[vl];
-            const double target = vu * Rspec;
-            const double *acc = sh.acc[vl];
-            uint32_t c = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int ci = 4 * (l & 3) + i;
-                c += ci < 14 && !(target < acc[ci < 14 ? ci : 13]) ? 1u : 0u;
-            }
-            c = quad_total(c);
-            if (vl >= nvalid) c = 14;
-            const uint32_t e = pack_event(c, mul_index(sh.usite[vl], c < 14 ? sh.hist[vl][c] : 0u));
-            vlo = c ? acc[c - 1] : 0.0;
-            vhi = c < 14 ? acc[c] : __builtin_inf();
+            const uint32_t e = line_event(vl, bound ? rbound : sh.rpred[s], vu, vlo, vhi);
 #pragma unroll
             for (int pp = 0; pp < P; ++pp)
                 place_packed<H>(pl[pp], bcast_quad(e, pp), l, &sh.selq[pp * rows + row], st);

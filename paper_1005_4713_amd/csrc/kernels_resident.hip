@@ -4,11 +4,10 @@
 //
 // What bounds it: a latency chain per cycle (LDS reads, barriers and, with more
 // than one workgroup, the R_max exchange); it reads nothing from memory but
-// other workgroups' words.  Per cycle, records included, against the three
-// launches per cycle it replaces: L = 16, d = 8 (one workgroup) 2.7 us against
-// 11.4, which were launches; L = 128, d = 8 (128 workgroups) 5.7 us against 77, of
-// which binning took 49 (a workgroup per line of 64 sites); L = 72, d = 8, two
-// colours 5.2 us against 58.
+// other workgroups' words.  Per cycle, records included: L = 16, d = 8 (one
+// workgroup) 2.7 us against 11.4 for three launches per cycle; L = 128, d = 8 (128
+// workgroups) 5.7 us against 16.5 (77 while those kernels kept their sums over
+// workgroups on one cache line); L = 72, d = 8, two colours 5.2 us (58 then).
 //
 // Layout in LDS, per domain of the workgroup:
 //   * one byte per site, octant-major in canonical order: 8 [up] + (up
@@ -680,7 +679,22 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     G = (g.K + D - 1) / D;
     uint64_t thr = D * g.lpd * gs;
     thr = (thr + 63) / 64 * 64 + 128;  // two service wavefronts beside the lines'
-    thr = thr < 256 ? 256 : thr > 1024 ? 1024 : thr;
+    // few lines of large octants: threads for the set-up of every site (about 1.4 us for
+    // each site of a thread; a run of two cycles of one domain of 24^3: 94 us with 256
+    // threads, 51 with 640)
+    const uint64_t sites = D * 8 * g.h3;
+    const uint64_t least = sites > 32 * 256 ? 640 : 256;
+    thr = thr < least ? least : thr > 1024 ? 1024 : thr;
+    // Shorter runs take the per-cycle kernels: the set-up (1.3 to 1.9 us per site of a
+    // thread, and 30 for a cooperative launch of several workgroups) against what a cycle
+    // saves, in us as measured over runs of 1 to 32 cycles from 16^3 to 128^3: 10.7 of 13
+    // for the smallest lattices, 12 of 16.5 with 4096 lines, 25 of 29 with an octant of
+    // 16^3 bytes, 90 of 95 with one of 20^3 bits.  Either side of the line, run and
+    // observables: 16^3 (d = 8) two cycles 35 us here, 45 on chip, three 73 and 47;
+    // 64^3 (d = 8) six 99 and 113, twelve 173 and 141.
+    const double setup = 1.5 * (double)sites / (double)thr + (G > 1 ? 30.0 : 0.0);
+    const double saved = 8.0 + (double)lines / 1100.0 + (double)g.h3 * (g.layout == SPKMC_LAYOUT_PACKED ? 0.010 : 0.004);
+    out.min_cycles = (uint64_t)(setup / saved) + 1;
     out.G = (int)G;
     out.D = (int)D;
     out.gs = gs;

@@ -14,6 +14,7 @@ struct ResidentShape {
     int G, D;        // workgroups, domains per workgroup
     int gs, block;   // lanes per frequency line, threads per workgroup
     size_t lds;      // bytes of LDS per workgroup
+    uint64_t min_cycles;  // shorter runs take the per-cycle kernels
 };
 
 struct ResidentArgs {

@@ -429,9 +429,10 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
         c->primed_grid = c->grid;
         c->cycle += ncycles;
         c->primed_cycle = c->cycle;
-    } else if (c->res.ok && !capturing(c->stream)) {
+    } else if (c->res.ok && ncycles >= c->res.min_cycles && !capturing(c->stream)) {
         // the lattice fits on chip: the cycles in one launch (a stream capture takes no
-        // cooperative launch and gets the per-cycle kernels below)
+        // cooperative launch and, like a run too short to repay the set-up, gets the
+        // per-cycle kernels below)
         const bool primed = c->primed_grid == c->res.G && c->primed_cycle == c->cycle && c->primed_span >= 2;
         e = launch_resident(c->g, c->res, c->cycle, ncycles, obs_every, !primed, c->stream);
         if (e != hipSuccess) {

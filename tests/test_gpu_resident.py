@@ -95,3 +95,12 @@ def test_octants_too_large_for_a_workgroup(spkmc, variant):
     print("case per-cycle kernels", variant, flush=True)
     gpu, orc = _pair(spkmc, 112, 56, "int8", variant, H=-0.05)
     _advance(gpu, orc, (3, 4), 1)
+
+
+@pytest.mark.parametrize("L,d,layout", [(16, 8, "int8"), (24, 24, "int8"), (64, 8, "int8"), (40, 40, "packed")])
+def test_short_and_long_runs(spkmc, L, d, layout):
+    """Runs too short to repay the on-chip set-up take the per-cycle kernels: lengths on
+    both sides of the line in turn, each continuing where the other stopped."""
+    print("case short and long runs", L, d, layout, flush=True)
+    gpu, orc = _pair(spkmc, L, d, layout, 0, H=0.05)
+    _advance(gpu, orc, (1, 12, 2, 3, 20, 1, 8, 4), 3)

@@ -84,7 +84,8 @@ enum { SPKMC_LAYOUT_INT8 = 0, SPKMC_LAYOUT_PACKED = 1 };
  * CYCLE: any layout and size (the only engine for lattices of 2^34 sites or
  * more): three launches per cycle (bin, select-and-flip, finalize), or, where
  * INT8 lattices and PACKED ones with an octant edge other than 8 and 16 fit in
- * the chip's LDS (a byte per site), one launch per spkmc_run call.
+ * the chip's LDS (a byte per site), one launch per spkmc_run call that is long
+ * enough to repay its set-up (some cycles, by the lattice's shape).
  * PERSISTENT: one cooperative launch per spkmc_run call with a device-wide R_max
  * exchange every cycle (PACKED layout, h = 8 or 16); every cycle bins the
  * active octant of every domain afresh.  With h = 16 and more lines than one

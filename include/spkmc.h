@@ -86,7 +86,7 @@ enum { SPKMC_LAYOUT_INT8 = 0, SPKMC_LAYOUT_PACKED = 1 };
  * INT8 lattices and PACKED ones with an octant edge other than 8 and 16 fit in
  * the chip's LDS (a byte per site), one launch per spkmc_run call that is long
  * enough to repay its set-up (some cycles, by the lattice's shape).
- * PERSISTENT: one cooperative launch per spkmc_run call with a device-wide R_max
+ * PERSISTENT: one launch per spkmc_run call with a device-wide R_max
  * exchange every cycle (PACKED layout, h = 8 or 16); every cycle bins the
  * active octant of every domain afresh.  With h = 16 and more lines than one
  * round of passes holds (up to 131 072 lines, e.g. two colours at L = 1024), the
@@ -102,6 +102,10 @@ enum { SPKMC_LAYOUT_INT8 = 0, SPKMC_LAYOUT_PACKED = 1 };
  * for PACKED lattices with domain 32) and follow every flip; a cycle reads the
  * counts of its active octant (of every octant with RMAX_ALL) instead of
  * binning it, and classifies only the slab that holds the selected site.
+ * Cooperative launches of a process run one after the other, whatever their
+ * streams.  A lattice that takes one workgroup is launched without them, at most
+ * 4096 cycles at a time, so that a cooperative launch of another stream finds
+ * room between two of its launches.
  * All engines produce bit-identical trajectories. */
 enum { SPKMC_ENGINE_AUTO = 0, SPKMC_ENGINE_CYCLE = 1, SPKMC_ENGINE_PERSISTENT = 2, SPKMC_ENGINE_INCREMENTAL = 3,
        SPKMC_ENGINE_SLAB = 4 };

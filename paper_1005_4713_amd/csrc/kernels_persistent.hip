@@ -1067,7 +1067,8 @@ PersistScratch scratch_of(const Geom &g, int G) {
 
 // Every workgroup of the launch resident at once.  A single workgroup waits for no
 // other and needs no cooperative dispatch (54 -> 34 us for one cycle of a 32^3
-// lattice and its observables); a stream capture refuses both forms, as ever.
+// lattice and its observables); spkmc_run keeps such launches short, since they run
+// beside cooperative ones.  A stream capture refuses both forms, as ever.
 hipError_t launch_resident_grid(const void *kern, int grid, int block, void **args, hipStream_t stream) {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (grid == 1 && hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone)

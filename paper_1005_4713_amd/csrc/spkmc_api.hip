@@ -292,45 +292,61 @@ static bool capturing(hipStream_t stream) {
     return cs != hipStreamCaptureStatusNone;
 }
 
+// ncycles cycles in one launch: the persistent and slab engines, and the on-chip launch
+// of the per-cycle engine.
+static spkmc_status run_launch(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
+    const bool on_chip = c->engine == SPKMC_ENGINE_CYCLE, slab = c->engine == SPKMC_ENGINE_SLAB;
+    const int grid = on_chip ? c->res.G : c->grid;
+    // the set-up of the sync words is needed unless the previous launch left
+    // them ready for this one
+    const bool primed = c->primed_grid == grid && c->primed_cycle == c->cycle && c->primed_span >= 2;
+    const bool current = c->counts_current;
+    c->counts_current = false;
+    hipError_t e;
+    if (on_chip)
+        e = launch_resident(c->g, c->res, c->cycle, ncycles, obs_every, !primed, c->stream);
+    else if (slab)
+        e = launch_slab(c->g, c->cycle, ncycles, obs_every, grid, !primed, current, c->stream);
+    else
+        e = launch_persistent(c->g, c->cycle, ncycles, obs_every, grid, c->block, c->wg_domains,
+                              c->engine == SPKMC_ENGINE_INCREMENTAL, !primed, c->stream);
+    if (e != hipSuccess) {
+        c->primed_grid = 0;
+        return hip_fail(c, e, on_chip ? "on-chip kernel launch" : slab ? "slab kernel launch" : "persistent kernel launch");
+    }
+    c->counts_current = slab;
+    c->primed_span = (primed ? c->primed_span : 0) + ncycles;
+    c->primed_grid = grid;
+    c->cycle += ncycles;
+    c->primed_cycle = c->cycle;
+    return SPKMC_OK;
+}
+
+// Most cycles of a launch of one workgroup.  Such a launch is a plain dispatch, which may
+// run beside a cooperative one of another stream and holds the compute unit that the last
+// workgroup of that one needs, while those already there wait for it, for 2 s at most: a
+// 346 ms run kept a 1024^3 run beside it waiting until its own end.  A cycle of one
+// workgroup takes 2.4 us (16^3) to about 45 (512 lines of 16^3 sites), so this is 0.2 s at
+// most and the other run starts between two launches; a launch costs about 10 us.
+constexpr uint64_t kPlainCycles = 4096;
+
 spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
     if (!c) return fail(nullptr, SPKMC_E_INVAL, "ctx is NULL");
     if (c->failed || !c->dev) return fail(c, SPKMC_E_STATE, "context is in a failed state");
     if (ncycles == 0) return SPKMC_OK;
     hipError_t e = hipSuccess;
-    if (c->engine != SPKMC_ENGINE_CYCLE) {
-        // the set-up of the sync words is needed unless the previous launch left
-        // them ready for this one
-        const bool primed = c->primed_grid == c->grid && c->primed_cycle == c->cycle && c->primed_span >= 2;
-        const bool current = c->counts_current;
-        c->counts_current = false;
-        if (c->engine == SPKMC_ENGINE_SLAB)
-            e = launch_slab(c->g, c->cycle, ncycles, obs_every, c->grid, !primed, current, c->stream);
-        else
-            e = launch_persistent(c->g, c->cycle, ncycles, obs_every, c->grid, c->block, c->wg_domains,
-                                  c->engine == SPKMC_ENGINE_INCREMENTAL, !primed, c->stream);
-        if (e != hipSuccess) {
-            c->primed_grid = 0;
-            return hip_fail(c, e, c->engine == SPKMC_ENGINE_SLAB ? "slab kernel launch" : "persistent kernel launch");
+    // a lattice that fits on chip: its cycles in one launch too (a stream capture takes no
+    // cooperative launch and, like a run too short to repay the set-up, gets the
+    // per-cycle kernels below)
+    const bool on_chip = c->engine == SPKMC_ENGINE_CYCLE && c->res.ok && ncycles >= c->res.min_cycles && !capturing(c->stream);
+    if (c->engine != SPKMC_ENGINE_CYCLE || on_chip) {
+        const uint64_t most = (on_chip ? c->res.G : c->grid) == 1 ? kPlainCycles : ncycles;
+        for (uint64_t left = ncycles; left;) {
+            const uint64_t n = std::min(left, most);
+            const spkmc_status st = run_launch(c, n, obs_every);
+            if (st != SPKMC_OK) return st;
+            left -= n;
         }
-        c->counts_current = c->engine == SPKMC_ENGINE_SLAB;
-        c->primed_span = (primed ? c->primed_span : 0) + ncycles;
-        c->primed_grid = c->grid;
-        c->cycle += ncycles;
-        c->primed_cycle = c->cycle;
-    } else if (c->res.ok && ncycles >= c->res.min_cycles && !capturing(c->stream)) {
-        // the lattice fits on chip: the cycles in one launch (a stream capture takes no
-        // cooperative launch and, like a run too short to repay the set-up, gets the
-        // per-cycle kernels below)
-        const bool primed = c->primed_grid == c->res.G && c->primed_cycle == c->cycle && c->primed_span >= 2;
-        e = launch_resident(c->g, c->res, c->cycle, ncycles, obs_every, !primed, c->stream);
-        if (e != hipSuccess) {
-            c->primed_grid = 0;
-            return hip_fail(c, e, "on-chip kernel launch");
-        }
-        c->primed_span = (primed ? c->primed_span : 0) + ncycles;
-        c->primed_grid = c->res.G;
-        c->cycle += ncycles;
-        c->primed_cycle = c->cycle;
     } else {
         c->primed_grid = 0;
         // PACKED lattices with octant edge 16 run the slab kernels, whose counts in the

@@ -74,6 +74,9 @@ struct spkmc_ctx {
     uint64_t primed_cycle, primed_span;
     // the slab counts in the state belong to the spins (slab engine, per-cycle slab kernels)
     bool counts_current;
+    // a captured initialisation or run may be replayed at any time, without a call here:
+    // the sync words, and after an initialisation the counts, are never taken as left
+    bool init_captured, run_captured;
     int engine;
     spkmc::ResidentShape res;      // CYCLE engine: the on-chip launch, where the lattice fits
     int grid, block, wg_domains;

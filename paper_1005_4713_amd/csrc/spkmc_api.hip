@@ -141,6 +141,15 @@ void spkmc::obs_from_state(const spkmc_params &p, uint64_t N, const DevState &st
     out->ur = tot ? (double)st.fired / (double)tot : 0.0;
 }
 
+static bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cs != hipStreamCaptureStatusNone;
+}
+
 #pragma GCC visibility push(default)
 extern "C" {
 
@@ -274,6 +283,7 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     }
 
     if (c->engine == SPKMC_ENGINE_CYCLE) (void)resident_configure(g, c->res);
+    c->init_captured = capturing(c->stream);
 
     hipError_t e;
     if ((e = launch_clear(g, lp.off_spin, c->stream)) != hipSuccess) return hip_fail(c, e, "clear kernel");
@@ -283,15 +293,6 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     return SPKMC_OK;
 }
 
-static bool capturing(hipStream_t stream) {
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return cs != hipStreamCaptureStatusNone;
-}
-
 // ncycles cycles in one launch: the persistent and slab engines, and the on-chip launch
 // of the per-cycle engine.
 static spkmc_status run_launch(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
@@ -299,8 +300,9 @@ static spkmc_status run_launch(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_ever
     const int grid = on_chip ? c->res.G : c->grid;
     // the set-up of the sync words is needed unless the previous launch left
     // them ready for this one
-    const bool primed = c->primed_grid == grid && c->primed_cycle == c->cycle && c->primed_span >= 2;
-    const bool current = c->counts_current;
+    const bool primed = c->primed_grid == grid && c->primed_cycle == c->cycle && c->primed_span >= 2 &&
+                        !c->init_captured && !c->run_captured;
+    const bool current = c->counts_current && !c->init_captured;
     c->counts_current = false;
     hipError_t e;
     if (on_chip)
@@ -352,8 +354,9 @@ spkmc_status spkmc_run(spkmc_ctx *c, uint64_t ncycles, uint32_t obs_every) {
         // PACKED lattices with octant edge 16 run the slab kernels, whose counts in the
         // state follow every flip: binned only when something else changed the spins
         // (a captured run bins for itself, and leaves nothing to the runs outside it)
-        const bool slab = slab_rows_supported(c->g), captured = slab && capturing(c->stream);
-        const bool current = c->counts_current && !captured;
+        const bool slab = slab_rows_supported(c->g), captured = capturing(c->stream);
+        const bool current = c->counts_current && !captured && !c->init_captured;
+        c->run_captured |= captured;
         c->counts_current = false;
         if (slab && !current && (e = launch_slab_bin(c->g, c->stream)) != hipSuccess)
             return hip_fail(c, e, "slab count kernel");

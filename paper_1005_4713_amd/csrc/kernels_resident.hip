@@ -702,9 +702,10 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     out.lds = (size_t)(kHeadBytes + D * per_domain);
     if (G == 1) out.lds += (size_t)(32 * lines + 32);  // the lines' numbers, two cycles of them
     void *kern = resident_kernel(gs, out.block);
-    (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)out.lds);
+    // the limit is the kernel's, for every context that launches it: the device's own
     int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, out.block, out.lds) != hipSuccess || occ < 1) {
+    if (hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, out.block, out.lds) != hipSuccess || occ < 1) {
         (void)hipGetLastError();
         return false;
     }

@@ -29,6 +29,7 @@
 // neighbouring domains it does not own to its own sites: at the end of the cycle
 // where the next colour makes them matter, else while the next maxima travel.
 // The records carry their cycle, so no flip has to be waited for.
+#include <algorithm>
 #include <string>
 
 #include "persistent_common.hpp"
@@ -662,10 +663,12 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     const int gs = ow <= 128 ? 16 : 64;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
     if (lines >= (1u << 20)) return false;  // a cycle's packed counters
-    // one workgroup while its wavefronts take the lines in a few rounds (no exchange);
-    // else as many as give each a round of kLinesPerWg lines, up to one per CU
+    // one workgroup while its lines are one round of 640 threads (no exchange); else as many
+    // as give each a round of kResidentLines lines, up to one per CU.  64 lines of 4^3 sites
+    // (32^3) take 4.3 us per cycle in one workgroup and 3.9 in two, after a set-up of 110 us
+    // and 80; with four lines per domain 13.7 and 4.3 (12.5 on the per-cycle kernels)
     uint64_t G = 1;
-    if (g.K * per_domain + 32 * lines + 64 > (uint64_t)lds - kHeadBytes || lines * gs > 4096) {
+    if (g.K * per_domain + 32 * lines + 64 > (uint64_t)lds - kHeadBytes || lines * gs > 512) {
         const uint64_t per_wg = gs == 16 ? kResidentLines : 14;  // 14 groups of 64 lanes and the service wavefronts
         G = (lines + per_wg - 1) / per_wg;
         const uint64_t need = (g.K + room - 1) / room;
@@ -680,20 +683,29 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     uint64_t thr = D * g.lpd * gs;
     thr = (thr + 63) / 64 * 64 + 128;  // two service wavefronts beside the lines'
     // few lines of large octants: threads for the set-up of every site (about 1.4 us for
-    // each site of a thread; a run of two cycles of one domain of 24^3: 94 us with 256
-    // threads, 51 with 640)
+    // each site of a thread; a run of two cycles of one domain of 24^3: 96 us with 256
+    // threads, 49.5 with 640)
     const uint64_t sites = D * 8 * g.h3;
     const uint64_t least = sites > 32 * 256 ? 640 : 256;
     thr = thr < least ? least : thr > 1024 ? 1024 : thr;
-    // Shorter runs take the per-cycle kernels: the set-up (1.3 to 1.9 us per site of a
-    // thread, and 30 for a cooperative launch of several workgroups) against what a cycle
-    // saves, in us as measured over runs of 1 to 32 cycles from 16^3 to 128^3: 10.7 of 13
-    // for the smallest lattices, 12 of 16.5 with 4096 lines, 25 of 29 with an octant of
-    // 16^3 bytes, 90 of 95 with one of 20^3 bits.  Either side of the line, run and
-    // observables: 16^3 (d = 8) two cycles 35 us here, 45 on chip, three 73 and 47;
-    // 64^3 (d = 8) six 99 and 113, twelve 173 and 141.
-    const double setup = 1.5 * (double)sites / (double)thr + (G > 1 ? 30.0 : 0.0);
-    const double saved = 8.0 + (double)lines / 1100.0 + (double)g.h3 * (g.layout == SPKMC_LAYOUT_PACKED ? 0.010 : 0.004);
+    // Shorter runs take the per-cycle kernels: the set-up against what a cycle saves, in us,
+    // fitted to run and observables over 1 to 48 cycles of 53 shapes from 4^3 to 240^3 in
+    // four variants.  The set-up: 33 for a cooperative launch, and per site of a thread 1.4
+    // (one workgroup) or 1.8, but at least 3 ns per site where the layers of a byte lattice
+    // are multiples of 4 KB apart.  A cycle here takes 2 to 12; of the per-cycle kernels, 11
+    // and what grows with the lines, and with the longest search for a site among them:
+    // over half an octant for one line, and with the fixed bound a line may have no event
+    // at all, over a whole one for many.  The maximum over all octants bins eight times as
+    // much.  Over those runs no choice is more than 1.11 times slower than the kernels it
+    // replaced, or than 1.35 times the better of the two here.
+    const bool packed = g.layout == SPKMC_LAYOUT_PACKED, all = g.variant & SPKMC_VARIANT_RMAX_ALL;
+    const bool bound = g.variant & SPKMC_VARIANT_RMAX_BOUND;
+    const double h3 = (double)g.h3, m = (double)lines, per_thread = (double)sites / (double)thr;
+    double setup = 7.0 + 1.4 * per_thread + 0.004 * h3;
+    if (G > 1) setup = 33.0 + std::max(1.8 * per_thread, !packed && g.L % 64 == 0 ? 0.003 * (double)sites : 0.0);
+    double saved = (G > 1 ? 7.5 : 8.0) - (bound ? 1.0 : 0.0) + m / 1100.0 + m * h3 * (packed ? 1.5e-5 : 5e-6);
+    saved += h3 * (packed ? 0.018 : 0.0075) * m / (m + (bound ? 2.4 : 1.0));
+    if (all) saved += 1.5 + h3 * (packed ? 0.0235 : 0.008) + m * h3 * (packed ? 6.5e-5 : 2.1e-5);
     out.min_cycles = (uint64_t)(setup / saved) + 1;
     out.G = (int)G;
     out.D = (int)D;

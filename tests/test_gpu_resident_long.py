@@ -1,6 +1,5 @@
 """The on-chip launch (kernels_resident.hip) of several workgroups over runs long enough
-to take it: with eight colours its shortest run is 4 cycles (40^3, d = 4) to 17 (100^3,
-d = 20).  Launches that follow one another without a new set-up, over both parities of
+to take it (its shortest run goes up to about 40 cycles, by the shape).  Launches that follow one another without a new set-up, over both parities of
 every bank of slots, counters and records; launches after spins were set and states
 restored.  Against the CPU oracle, every spin, counter and
 record; the clock within 1e-12 relative (the device has its own logarithm)."""
@@ -15,6 +14,10 @@ T_REL = 1e-12
 RMAX_ALL, TWO, BOUND = 1, 2, 4
 SHAPES = [(40, 4, "int8"), (64, 8, "int8"), (72, 8, "packed"), (90, 10, "int8"), (96, 24, "packed"), (64, 32, "int8"),
           (80, 40, "int8"), (100, 20, "int8"), (128, 8, "int8")]
+# few lines: one workgroup up to one round of them (32 of 16 lanes, 8 of 64), else two and
+# more; with four lines per domain each has four times as many
+FEW = [(8, 2, "int8"), (12, 4, "int8"), (16, 4, "int8"), (24, 4, "int8"), (24, 8, "int8"), (32, 8, "int8"),
+       (40, 8, "packed"), (36, 12, "int8"), (48, 16, "int8"), (40, 20, "int8"), (60, 20, "int8"), (48, 24, "packed")]
 
 
 @pytest.fixture(scope="module")
@@ -61,11 +64,11 @@ def _advance(gpu, orc, lengths, obs):
 
 
 @pytest.mark.parametrize("variant", [0, RMAX_ALL, BOUND, TWO])
-@pytest.mark.parametrize("L,d,layout", SHAPES)
+@pytest.mark.parametrize("L,d,layout", SHAPES + FEW)
 def test_launch_after_launch(spkmc, L, d, layout, variant):
     print("case launch after launch", L, d, layout, variant, flush=True)
     gpu, orc = _pair(spkmc, L, d, layout, variant)
-    _advance(gpu, orc, (19, 22, 21, 20), 3)
+    _advance(gpu, orc, (49, 42, 41, 20), 3)
 
 
 @pytest.mark.parametrize("L,d,layout", [(64, 8, "int8"), (72, 8, "packed"), (90, 10, "int8"), (96, 24, "packed")])

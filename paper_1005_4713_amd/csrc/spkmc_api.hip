@@ -214,7 +214,8 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
     g.rec = (spkmc_record *)(c->dev + lp.off_rec);
     g.Rk = (double *)(c->dev + lp.off_Rk);
     g.hist = (uint32_t *)(c->dev + lp.off_hist);
-    g.flip = (uint64_t *)(c->dev + lp.off_flip);
+    g.places = cycle_places(g);
+    g.flip = g.places == 1 ? g.st->sums : (uint64_t *)(c->dev + lp.off_flip);
     g.sync = (uint64_t *)(c->dev + lp.off_sync);
     g.dh = p->layout == SPKMC_LAYOUT_PACKED ? (uint64_t *)(c->dev + lp.off_dh) : nullptr;
     g.sc = p->layout == SPKMC_LAYOUT_PACKED && g.h == 16 ? (uint32_t *)(c->dev + lp.off_sc) : nullptr;
@@ -230,7 +231,6 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
         for (int cc = 1; cc < 14; ++cc)
             if (g.r[cc] > rb) rb = g.r[cc];
         g.rbound = (double)((int64_t)g.h * g.h * g.h) * rb;
-        g.pad2 = 0;
     }
     c->spin_off = lp.off_spin;
     c->spin_bytes = lp.spin_bytes;

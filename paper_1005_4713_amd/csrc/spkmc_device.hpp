@@ -2,6 +2,8 @@
 // gfx950 spkMC library (host and device code of the library include it; the
 // CPU oracle does not).
 #pragma once
+#include <type_traits>
+
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -22,7 +24,8 @@ struct alignas(256) DevState {
     uint64_t rec_count;    // records written (ring index = rec_count % record_cap)
     uint32_t error;        // non-zero: a device-side wait gave up (see kErr*)
     uint32_t pad0;
-    uint64_t pad1[24];
+    uint64_t sums[4];      // per-cycle engine: the one place of its sums over workgroups
+    uint64_t pad1[20];
 };
 static_assert(sizeof(DevState) == 256, "DevState must stay 256 bytes");
 
@@ -55,7 +58,7 @@ struct Geom {
     double r[14];          // rate table
     double rbound;         // R'_max = n_k max_c r_c (RMAX_BOUND)
     uint32_t lpd;          // frequency lines per domain and cycle: 1, or 4 (TWO_COLOURS)
-    uint32_t pad2;
+    uint32_t places;       // per-cycle engine: places of its sums (cycle_places)
 };
 
 // ---------------------------------------------------------------------------
@@ -139,15 +142,51 @@ __device__ inline int line_select(const uint32_t *cnt, const double *r, double t
 __device__ inline double bits_to_double(uint64_t b) { return __longlong_as_double((long long)b); }
 __device__ inline uint64_t double_to_bits(double v) { return (uint64_t)__double_as_longlong(v); }
 
-// The per-cycle engine's sums over workgroups, in the first K words of the flip
-// region: up to 64 places on cache lines of their own, each (fired, dM, dB, R_max),
-// a workgroup adding to place blockIdx mod the count.  (One place for all took
-// as long as the work at 2048^3: about 20 ns for each of 6144 atomics per cycle.)
-__device__ inline uint32_t cycle_places(const Geom &g) {
-    const uint32_t k = g.K >> 4;  // 16 words a place
-    return k >= 64 ? 64u : k ? 1u << (31 - __builtin_clz(k)) : 1u;
+// A value folded over the wavefront, in lane 63 (all lanes take part): DPP shifts within
+// each row of 16, then the last lane of each row carried into the rows above; lanes from
+// outside read 0.
+template <class F>
+__device__ inline uint64_t wave_fold(uint64_t v, F f) {
+    auto from = [&](auto ctrl, auto rows) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, decltype(ctrl)::value,
+                                                                  decltype(rows)::value, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), decltype(ctrl)::value,
+                                                                  decltype(rows)::value, 0xF, true);
+        v = f(v, ((uint64_t)hi << 32) | lo);
+    };
+    using std::integral_constant;
+    const integral_constant<int, 0xF> all;
+    from(integral_constant<int, 0x111>{}, all);  // row_shr 1, 2, 4, 8
+    from(integral_constant<int, 0x112>{}, all);
+    from(integral_constant<int, 0x114>{}, all);
+    from(integral_constant<int, 0x118>{}, all);
+    from(integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});  // row_bcast 15 and 31
+    from(integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});
+    return v;
 }
-__device__ inline uint64_t *cycle_place(const Geom &g, uint32_t i) { return g.flip + 16 * (i & (cycle_places(g) - 1)); }
+__device__ inline uint64_t wave_total(uint64_t v) {
+    return wave_fold(v, [](uint64_t a, uint64_t b) { return a + b; });
+}
+__device__ inline uint64_t wave_largest(uint64_t v) {
+    return wave_fold(v, [](uint64_t a, uint64_t b) { return a > b ? a : b; });
+}
+
+// The per-cycle engine's sums over workgroups (fired, dM, dB, R_max): one place in the
+// state header, or, for many workgroups, up to 64 on cache lines of their own in the
+// first K words of the flip region, a workgroup adding to place blockIdx mod the count.
+// (One place for all took as long as the work at 2048^3: about 20 ns for each of 6144
+// atomics per cycle.  But the flip region is a page of its own: 0.5 us for the selection
+// and 0.6 for the bookkeeping, more than the atomics of a few workgroups.  256^3 with
+// octant edge 8, 16 workgroups: 24.5 us per cycle in the header, 24.9 in 8 places.)  The
+// row and slab kernels have 64 to 256 lines to a workgroup: a place for eight of them, from
+// 64 on; the generic ones, which the all-octant maximum may run on, 1 to 4.
+inline uint32_t cycle_places(const Geom &g) {  // set-up: g.places, and g.flip points to the first
+    const bool rows = g.layout == SPKMC_LAYOUT_PACKED && (g.h == 8 || g.h == 16) && !(g.variant & SPKMC_VARIANT_RMAX_ALL);
+    const uint32_t per_wg = g.h == 8 ? 256u : g.lpd == 1 ? 64u : 128u;
+    const uint32_t k = rows ? g.K * g.lpd / (8 * per_wg) : g.K >> 4;  // at least 16 words a place
+    return k >= 64 ? 64u : k >= 8 ? 1u << (31 - __builtin_clz(k)) : 1u;
+}
+__device__ inline uint64_t *cycle_place(const Geom &g, uint32_t i) { return g.flip + 16 * (i & (g.places - 1)); }
 __device__ inline void add_counters(const Geom &g, long long F, long long dM, long long dB) {
     unsigned long long *p = (unsigned long long *)cycle_place(g, blockIdx.x);
     if (F) atomicAdd(&p[0], (unsigned long long)F);
@@ -160,44 +199,53 @@ __device__ inline void raise_rmax(const Geom &g, unsigned long long bits) {  // 
 // R_max of the cycle (every lane of the wavefront takes part).
 __device__ inline double cycle_rmax(const Geom &g) {
     if (g.variant & SPKMC_VARIANT_RMAX_BOUND) return g.rbound;
-    double v = bits_to_double(cycle_place(g, threadIdx.x & 63)[3]);
-    for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
-    return v;
+    if (g.places == 1) return bits_to_double(g.flip[3]);
+    const uint64_t v = wave_largest(cycle_place(g, threadIdx.x & 63)[3]);
+    return bits_to_double(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+                          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63));
 }
 
 // Step 5 and the bookkeeping of cycle n on the per-cycle engine (one wavefront,
 // after every workgroup's selection and flips): the clock, the counters from the
-// sums, the observation record; the sums reset.
+// sums, the observation record; the sums reset.  A launch on every cycle's path: the
+// sums and the state travel together.
 __device__ inline void finalize_cycle(const Geom &g, uint64_t n, uint32_t obs_every) {
     DevState *st = g.st;
     const bool two = g.lpd == 4;
+    const uint32_t places = g.places;
+    uint64_t sum[4] = {0, 0, 0, 0};
+    uint64_t *const p = cycle_place(g, threadIdx.x);
+    if (threadIdx.x < places)
+        for (int i = 0; i < 4; ++i) sum[i] = p[i];
+    spkmc_record r;
+    r.cycle = n + 1;
+    r.fired = st->fired;
+    r.nulls = st->nulls;
+    r.t = st->t;
+    r.M = st->M;
+    r.B = st->B;
     const CycleDraw cd = cycle_draw(g.seed, n, two);
-    const double Rmax = cycle_rmax(g);
-    long long sum[3] = {0, 0, 0};
-    if (threadIdx.x < cycle_places(g)) {
-        uint64_t *p = cycle_place(g, threadIdx.x);
-        for (int i = 0; i < 3; ++i) sum[i] = (long long)p[i];
-        p[0] = p[1] = p[2] = p[3] = 0;
+    const double lnu = -log(cd.ut);
+    if (threadIdx.x < places) p[0] = p[1] = p[2] = p[3] = 0;
+    if (places > 1) {
+        for (int i = 0; i < 3; ++i) sum[i] = wave_total(sum[i]);
+        sum[3] = wave_largest(sum[3]);
     }
-    for (int o = 32; o > 0; o >>= 1)
-        for (int i = 0; i < 3; ++i) sum[i] += __shfl_xor(sum[i], o);
-    if (threadIdx.x != 0) return;
-    const double dt = -log(cd.ut) / ((two ? 2.0 : 8.0) * Rmax);
-    st->t = st->t + dt;
-    const uint64_t f = (uint64_t)sum[0];
-    st->fired += f;
-    st->nulls += (uint64_t)g.K * g.lpd - f;
-    st->M += sum[1];
-    st->B += sum[2];
-    st->cycle = n + 1;
+    if (threadIdx.x != (places > 1 ? 63u : 0u)) return;
+    const double Rmax = (g.variant & SPKMC_VARIANT_RMAX_BOUND) ? g.rbound : bits_to_double(sum[3]);
+    const uint64_t f = sum[0];
+    r.t = r.t + lnu / ((two ? 2.0 : 8.0) * Rmax);
+    r.fired += f;
+    r.nulls += (uint64_t)g.K * g.lpd - f;
+    r.M += (int64_t)sum[1];
+    r.B += (int64_t)sum[2];
+    st->cycle = r.cycle;
+    st->fired = r.fired;
+    st->nulls = r.nulls;
+    st->t = r.t;
+    st->M = r.M;
+    st->B = r.B;
     if (obs_every && ((n + 1) % obs_every) == 0 && g.rec_cap) {
-        spkmc_record r;
-        r.cycle = n + 1;
-        r.fired = st->fired;
-        r.nulls = st->nulls;
-        r.t = st->t;
-        r.M = st->M;
-        r.B = st->B;
         g.rec[st->rec_count % g.rec_cap] = r;
         st->rec_count += 1;
     }

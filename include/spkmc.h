@@ -208,14 +208,18 @@ spkmc_status spkmc_init(const spkmc_params *p, void *dev_buf, size_t dev_bytes, 
 spkmc_status spkmc_run(spkmc_ctx *ctx, uint64_t ncycles, uint32_t obs_every);
 
 /* Synchronise the stream and return the current state: counters, clock (Sec. 3.1
- * step 5), M and B, the energy of eq. 1, m of eq. 4 and the utilisation of eq. 8. */
+ * step 5), M and B, the energy of eq. 1, m of eq. 4 and the utilisation of eq. 8.
+ * The first call of the process that reads a state (this, spkmc_records) allocates
+ * 16 KB of pinned host memory, kept until the process ends. */
 spkmc_status spkmc_observables(spkmc_ctx *ctx, spkmc_obs *out);
 
 /* Synchronise and copy the most recent min(cap, recorded, record_cap) records,
  * oldest first, to host memory; *n receives the number copied. */
 spkmc_status spkmc_records(spkmc_ctx *ctx, spkmc_record *host, size_t cap, size_t *n);
 
-/* Synchronise and copy all N spins (+1 / -1, index x + L (y + L z)) to host. */
+/* Synchronise and copy all N spins (+1 / -1, index x + L (y + L z)) to host.
+ * From 2^21 sites the conversion of PACKED spins runs on up to eight host threads
+ * (seven started for the call); likewise spkmc_set_spins in either layout. */
 spkmc_status spkmc_copy_spins(spkmc_ctx *ctx, int8_t *host, size_t n);
 
 /* Replace all N spins from host memory (values +1 / -1) and recompute M and B;

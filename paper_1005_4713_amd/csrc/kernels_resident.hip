@@ -6,8 +6,8 @@
 // than one workgroup, the R_max exchange); it reads nothing from memory but
 // other workgroups' words.  Per cycle, records included: L = 16, d = 8 (one
 // workgroup) 2.7 us against 11.4 for three launches per cycle; L = 128, d = 8 (128
-// workgroups) 5.7 us against 16.5 (77 while those kernels kept their sums over
-// workgroups on one cache line); L = 72, d = 8, two colours 5.2 us (58 then).
+// workgroups) 5.7 us against 16.2 (77 while those kernels kept their sums over
+// workgroups on one cache line); L = 72, d = 8, two colours 5.2 us against 18.0 (58 then).
 //
 // Layout in LDS, per domain of the workgroup:
 //   * one byte per site, octant-major in canonical order: 8 [up] + (up

@@ -20,14 +20,14 @@ constexpr uint32_t kNoEvent = 0xFFFFFFFFu;
 
 // Device scratch of the persistent engine (its own region of the state).
 struct PersistScratch {
-    uint64_t *slot;     // 2 x G: R_max of each workgroup, generation bit 63 (each in its own place, slot_at)
+    uint64_t *slot;     // 2 x G: R_max of each workgroup, generation bit 63 (slot i at word i << slot_shift)
     uint64_t *flag;     // G: cycles whose flips are complete (likewise)
     int64_t *recp;      // kRecBanks x G x 3: counter partials (fired, dM, dB) since launch start
     int64_t *fin;       // G x 3: each workgroup's totals (fired, dM, dB) at the end of the launch
     uint64_t *emitted;  // records of this launch appended so far (fixed-bound variant); 0 between launches
     double *rpred;      // 8: the last R_max of each colour, the next launch's first predictions
 };
-constexpr uint64_t kScratchWordsPerWg = 2 + 1 + 3 * kRecBanks + 3;
+constexpr uint64_t kScratchWordsPerWg = 2 + 1 + 3 * kRecBanks + 3;  // (the first three, once slots and flags, are unused)
 
 // The slots and flags lie in the histogram region of the state (8 words per line, of no
 // other use to the persistent engines), 64 bytes apart: a store to a line that other

@@ -106,8 +106,8 @@ static LayoutPlan plan(const spkmc_params *p) {
     lp.off_Rk = o; o = align256(o + lines * 8);
     lp.off_hist = o; o = align256(o + lines * 64);
     lp.off_flip = o; o = align256(o + K * 8);
-    // persistent engine: slots, flags and record partials of its workgroups, and
-    // the class changes its workgroups push to one another (PACKED)
+    // persistent engine: record partials and totals of its workgroups, and the class
+    // changes its workgroups push to one another (PACKED)
     lp.off_sync = o; o = align256(o + persistent_scratch_words(lines) * 8);
     lp.off_dh = o;
     if (p->layout == SPKMC_LAYOUT_PACKED) o = align256(o + K * 16 * 8);

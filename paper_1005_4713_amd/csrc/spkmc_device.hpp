@@ -46,9 +46,10 @@ struct Geom {
     DevState *st;
     spkmc_record *rec;
     double *Rk;            // K
-    uint32_t *hist;        // K x 16 (14 used)
+    uint32_t *hist;        // 16 words per line: histograms (14 used) of the per-cycle engine; the slots
+                           // and flags of the persistent engines; the on-chip launch's exchange words
     uint64_t *flip;        // per-cycle engine: sums over workgroups (cycle_place)
-    uint64_t *sync;        // persistent engine: R_max slots, flags, record partials (9 G words)
+    uint64_t *sync;        // persistent engine: record partials, totals, predictions (PersistScratch)
     uint64_t *dh;          // PACKED: class changes pushed across workgroups, K x 8 octants x 2 spins
     uint32_t *sc;          // PACKED, h = 16: per octant the class counts of its four 4-plane slabs (28 words)
     int8_t *spin8;         // INT8 spins

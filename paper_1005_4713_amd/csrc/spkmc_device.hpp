@@ -180,12 +180,14 @@ __device__ inline uint64_t wave_largest(uint64_t v) {
 // and 0.6 for the bookkeeping, more than the atomics of a few workgroups.  256^3 with
 // octant edge 8, 16 workgroups: 24.5 us per cycle in the header, 24.9 in 8 places.)  The
 // row and slab kernels have 64 to 256 lines to a workgroup: a place for eight of them, from
-// 64 on; the generic ones, which the all-octant maximum may run on, 1 to 4.
+// 64 on.  The generic ones, which the all-octant maximum may run on, have 1 to 4 (40^3, d = 8,
+// two colours, 500 lines: 13 us per cycle in 4 places, 19 in the header).
 inline uint32_t cycle_places(const Geom &g) {  // set-up: g.places, and g.flip points to the first
     const bool rows = g.layout == SPKMC_LAYOUT_PACKED && (g.h == 8 || g.h == 16) && !(g.variant & SPKMC_VARIANT_RMAX_ALL);
     const uint32_t per_wg = g.h == 8 ? 256u : g.lpd == 1 ? 64u : 128u;
-    const uint32_t k = rows ? g.K * g.lpd / (8 * per_wg) : g.K >> 4;  // at least 16 words a place
-    return k >= 64 ? 64u : k >= 8 ? 1u << (31 - __builtin_clz(k)) : 1u;
+    const uint32_t lines = g.K * g.lpd, k = rows ? lines / (8 * per_wg) : g.K >> 4;  // at least 16 words a place
+    if (rows ? k < 8 : lines < 128 || !k) return 1u;
+    return k >= 64 ? 64u : 1u << (31 - __builtin_clz(k));
 }
 __device__ inline uint64_t *cycle_place(const Geom &g, uint32_t i) { return g.flip + 16 * (i & (g.places - 1)); }
 __device__ inline void add_counters(const Geom &g, long long F, long long dM, long long dB) {

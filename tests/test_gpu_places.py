@@ -34,9 +34,9 @@ def test_packed(spkmc, L, d, variant):
     assert np.array_equal(a.spins(), b.spins())
 
 
-# 4 lines to a workgroup of the selection: 125 domains one place, 216 eight; the all-octant
-# maximum of packed lattices
-@pytest.mark.parametrize("L,d,layout,variant", [(40, 8, "int8", 0), (48, 8, "int8", 0), (48, 8, "int8", 2), (48, 8, "int8", 1),
+# 1 to 4 lines to a workgroup: up to 127 lines one place, 64 domains with two colours four,
+# 216 domains eight; the all-octant maximum of packed lattices
+@pytest.mark.parametrize("L,d,layout,variant", [(40, 8, "int8", 0), (32, 8, "int8", 2), (40, 8, "int8", 2), (48, 8, "int8", 0), (48, 8, "int8", 2), (48, 8, "int8", 1),
                                                 (80, 16, "packed", 1), (96, 16, "packed", 1), (128, 8, "int8", 0)])
 def test_generic(spkmc, L, d, layout, variant):
     print("case places generic", L, d, layout, variant, flush=True)

@@ -663,12 +663,18 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     const int gs = ow <= 128 ? 16 : 64;
     const uint64_t lines = (uint64_t)g.K * g.lpd;
     if (lines >= (1u << 20)) return false;  // a cycle's packed counters
-    // one workgroup while its lines are one round of 640 threads (no exchange); else as many
-    // as give each a round of kResidentLines lines, up to one per CU.  64 lines of 4^3 sites
-    // (32^3) take 4.3 us per cycle in one workgroup and 3.9 in two, after a set-up of 110 us
-    // and 80; with four lines per domain 13.7 and 4.3 (12.5 on the per-cycle kernels)
+    // one workgroup while its wavefronts take the lines in two rounds, one with the
+    // all-octant maximum (no exchange; launches of one workgroup on several streams run side
+    // by side, cooperative ones one after the other: 8 lattices of 32^3, d = 8, on as many
+    // threads 10 us per cycle of all so, 38 in two workgroups each, 23 on the per-cycle
+    // kernels); else as many as give each a round of kResidentLines lines, up to one per CU.
+    // One lattice, us per cycle in one workgroup, in several, and on the per-cycle kernels:
+    // 64 lines of 4^3 sites 4.3, 3.9 and 11.4; 125 lines 7.7, 4.0 and 11.6; 256 lines (two
+    // colours) 13.7, 4.3 and 12.5; the all-octant maximum 64 lines 8.0, 6.2 and 15.3, 125
+    // lines 15.0, 6.3 and 15.6
+    const bool all = g.variant & SPKMC_VARIANT_RMAX_ALL;
     uint64_t G = 1;
-    if (g.K * per_domain + 32 * lines + 64 > (uint64_t)lds - kHeadBytes || lines * gs > 512) {
+    if (g.K * per_domain + 32 * lines + 64 > (uint64_t)lds - kHeadBytes || lines * gs > (all ? 1024u : 2048u)) {
         const uint64_t per_wg = gs == 16 ? kResidentLines : 14;  // 14 groups of 64 lanes and the service wavefronts
         G = (lines + per_wg - 1) / per_wg;
         const uint64_t need = (g.K + room - 1) / room;
@@ -691,21 +697,23 @@ bool resident_configure(const Geom &g, ResidentShape &out) {
     // Shorter runs take the per-cycle kernels: the set-up against what a cycle saves, in us,
     // fitted to run and observables over 1 to 48 cycles of 53 shapes from 4^3 to 240^3 in
     // four variants.  The set-up: 33 for a cooperative launch, and per site of a thread 1.4
-    // (one workgroup) or 1.8, but at least 3 ns per site where the layers of a byte lattice
-    // are multiples of 4 KB apart.  A cycle here takes 2 to 12; of the per-cycle kernels, 11
-    // and what grows with the lines, and with the longest search for a site among them:
-    // over half an octant for one line, and with the fixed bound a line may have no event
-    // at all, over a whole one for many.  The maximum over all octants bins eight times as
-    // much.  Over those runs no choice is more than 1.11 times slower than the kernels it
-    // replaced, or than 1.35 times the better of the two here.
-    const bool packed = g.layout == SPKMC_LAYOUT_PACKED, all = g.variant & SPKMC_VARIANT_RMAX_ALL;
-    const bool bound = g.variant & SPKMC_VARIANT_RMAX_BOUND;
+    // (one workgroup of 640 threads) or 1.8, but at least 3 ns per site where the rows of a
+    // byte lattice are a power of two apart.  A cycle here takes 2 to 12, in one workgroup
+    // 0.04 (0.08) more per line after the first 16; of the per-cycle kernels, 11 and what
+    // grows with the lines, and with the longest search for a site among them: over half
+    // an octant for one line, and with the fixed bound a line may have no event at all, over
+    // a whole one for many.  The maximum over all octants bins eight times as much.  Over
+    // those runs no choice is more than 1.12 times slower than the kernels it replaced.
+    const bool packed = g.layout == SPKMC_LAYOUT_PACKED, bound = g.variant & SPKMC_VARIANT_RMAX_BOUND;
     const double h3 = (double)g.h3, m = (double)lines, per_thread = (double)sites / (double)thr;
+    const double strided = !packed && g.L % (G > 1 ? 64 : 32) == 0 ? 0.003 * (double)sites : 0.0;
     double setup = 7.0 + 1.4 * per_thread + 0.004 * h3;
-    if (G > 1) setup = 33.0 + std::max(1.8 * per_thread, !packed && g.L % 64 == 0 ? 0.003 * (double)sites : 0.0);
+    if (G > 1 || thr > 640) setup = (G > 1 ? 33.0 : 12.0) + std::max(1.8 * per_thread, strided);
     double saved = (G > 1 ? 7.5 : 8.0) - (bound ? 1.0 : 0.0) + m / 1100.0 + m * h3 * (packed ? 1.5e-5 : 5e-6);
     saved += h3 * (packed ? 0.018 : 0.0075) * m / (m + (bound ? 2.4 : 1.0));
     if (all) saved += 1.5 + h3 * (packed ? 0.0235 : 0.008) + m * h3 * (packed ? 6.5e-5 : 2.1e-5);
+    if (G == 1) saved -= (all ? 0.08 : 0.04) * std::max(0.0, m * gs / 16.0 - 16.0);
+    if (saved < 0.5) return false;
     out.min_cycles = (uint64_t)(setup / saved) + 1;
     out.G = (int)G;
     out.D = (int)D;

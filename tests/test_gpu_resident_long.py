@@ -14,8 +14,8 @@ T_REL = 1e-12
 RMAX_ALL, TWO, BOUND = 1, 2, 4
 SHAPES = [(40, 4, "int8"), (64, 8, "int8"), (72, 8, "packed"), (90, 10, "int8"), (96, 24, "packed"), (64, 32, "int8"),
           (80, 40, "int8"), (100, 20, "int8"), (128, 8, "int8")]
-# few lines: one workgroup up to one round of them (32 of 16 lanes, 8 of 64), else two and
-# more; with four lines per domain each has four times as many
+# few lines: one workgroup up to 128 of 16 lanes or 32 of 64 (half as many with the
+# all-octant maximum), else several; with two colours there are four times as many
 FEW = [(8, 2, "int8"), (12, 4, "int8"), (16, 4, "int8"), (24, 4, "int8"), (24, 8, "int8"), (32, 8, "int8"),
        (40, 8, "packed"), (36, 12, "int8"), (48, 16, "int8"), (40, 20, "int8"), (60, 20, "int8"), (48, 24, "packed")]
 
